@@ -1,6 +1,7 @@
 // C ABI of the library: argument checking, workspace layout and the device-step
 // entry points.  The sampler (causal controller) is in sampler.cpp.
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <string>
 
@@ -21,6 +22,18 @@ Status hip_status(hipError_t e, const char* what) {
 dc_status fail(const Status& s) {
   g_last_error = s.msg;
   return s.code;
+}
+
+int compute_units() {
+  static std::atomic<int> cus[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+  int n = cus[dev].load(std::memory_order_relaxed);
+  if (n == 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    cus[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
 }
 
 Status make_geo(const dc_model_cfg* cfg, Geo& g) {
@@ -69,7 +82,9 @@ Workspace workspace_layout(const Geo& g, int batch) {
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
   w.a = take(size_t(g.N) * g.d * g.esz);
-  w.qk = take(size_t(w.ldv + 64) * 2 * g.d * g.esz);   // padding rows for the attention's K tiles
+  // bf16: padding rows for the attention's K tiles; fp32: qkv [N, 3d] spans qk and vt (no gap
+  // between them: d is a multiple of 128)
+  w.qk = take(size_t(w.ldv + 64) * 2 * g.d * g.esz);
   w.vt = take(size_t(g.d) * w.ldv * g.esz);
   w.o = take(size_t(g.N) * g.d * g.esz);
   w.ff = take(size_t(g.N) * g.F * g.esz);
@@ -203,13 +218,13 @@ Status block_forward(const Geo& g, const dc_block_weights* bw, const float* mod,
       }
     } else {
       float* a = at<float>(ws, L.a);
-      float* qk = at<float>(ws, L.qk);
-      float* vt = at<float>(ws, L.vt);
+      float* qkv = at<float>(ws, L.qk);       // [N, 3d], over the qk and vt regions
       float* o = at<float>(ws, L.o);
       float* ff = at<float>(ws, L.ff);
       DC_TRY(ln_modulate(hb, N, d, shift1, scale1, a, d, false, g, s));
-      DC_TRY(gemm_f32_qkv(a, static_cast<const float*>(bw->w_qkv), bw->b_qkv, qk, vt, L.ldv, g, N, s));
-      DC_TRY(attention_f32(qk, vt, L.ldv, o, g, N, s));
+      DC_TRY(gemm_f32_bias_act(a, d, static_cast<const float*>(bw->w_qkv), d, bw->b_qkv, qkv, 3 * d, N,
+                               3 * d, d, Act::kNone, s));
+      DC_TRY(attention_f32(qkv, o, g, N, s));
       DC_TRY(gemm_f32_gate_residual(o, d, static_cast<const float*>(bw->w_o), d, bw->b_o, gate1, hb,
                                     d, N, d, d, s));
       DC_TRY(ln_modulate(hb, N, d, shift2, scale2, a, d, false, g, s));

@@ -1,7 +1,7 @@
 // Joint video + text self-attention, softmax(Q K^T / sqrt(d_h)) V per head, with
 // an online softmax (flash-style: the N x N score matrix never leaves registers).
 //
-// Two bf16 kernels: k_attn16 (head_dim 64, sequences of 8,192 tokens and more; see its
+// The bf16 model's kernels (the fp32 model's attention is in attention_f32.hip): k_attn16 (head_dim 64, sequences of 8,192 tokens and more; see its
 // own comment below) and k_attn_bf16 (head_dim 64 below that, and head_dim 72).
 //
 // k_attn_bf16 (gfx950 MFMA 32x32x16).  A workgroup is 4 waves x 32 query rows of one
@@ -689,49 +689,6 @@ k_attn16(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, int l
   }
 }
 
-// fp32 path: one thread per query row, key/value tiles of 64 tokens in LDS.
-template <int D>
-__global__ void __launch_bounds__(64) k_attn_f32(const float* __restrict__ qk,
-                                                 const float* __restrict__ vt, int ldv,
-                                                 float* __restrict__ out, int M, int d,
-                                                 float scale) {
-  __shared__ float sK[64][D + 1];
-  __shared__ float sV[64][D + 1];
-  const int head = blockIdx.y, tid = threadIdx.x;
-  const int q = blockIdx.x * 64 + tid;
-  const int ldq = 2 * d;
-  float qv[D], o[D];
-  for (int i = 0; i < D; ++i) {
-    qv[i] = q < M ? qk[size_t(q) * ldq + head * D + i] : 0.f;
-    o[i] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  for (int kv0 = 0; kv0 < M; kv0 += 64) {
-    for (int e = tid; e < 64 * D; e += 64) {
-      const int r = e / D, c = e % D;
-      const int kv = kv0 + r;
-      sK[r][c] = kv < M ? qk[size_t(kv) * ldq + d + head * D + c] : 0.f;
-      const int r2 = e % 64, c2 = e / 64;
-      sV[r2][c2] = (kv0 + r2) < M ? vt[size_t(head * D + c2) * ldv + kv0 + r2] : 0.f;
-    }
-    __syncthreads();
-    const int n = min(64, M - kv0);
-    for (int j = 0; j < n; ++j) {
-      float sc = 0.f;
-      for (int i = 0; i < D; ++i) sc += qv[i] * sK[j][i];
-      sc *= scale;
-      const float mn = fmaxf(m, sc);
-      const float a = expf(m - mn), p = expf(sc - mn);
-      l = l * a + p;
-      for (int i = 0; i < D; ++i) o[i] = o[i] * a + p * sV[j][i];
-      m = mn;
-    }
-    __syncthreads();
-  }
-  if (q < M)
-    for (int i = 0; i < D; ++i) out[size_t(q) * d + head * D + i] = o[i] / l;
-}
-
 }  // namespace
 
 // Resident workgroups of the bf16 attention kernel per XCD on the current device
@@ -806,16 +763,6 @@ Status attention_bf16(const uint16_t* qk, const uint16_t* vt, int ldv, uint16_t*
   if (g.Dh == 64) return launch_attn<64, false>(qk, vt, ldv, out, g, M, part, part_bytes, s);
   if (g.Dh == 72) return launch_attn<72, false>(qk, vt, ldv, out, g, M, part, part_bytes, s);
   return Status::shape("bf16 attention supports head_dim 64 and 72");
-}
-
-Status attention_f32(const float* qk, const float* vt, int ldv, float* out, const Geo& g, int M,
-                     hipStream_t s) {
-  if (g.Dh != 64) return Status::shape("fp32 attention supports head_dim 64");
-  const float scale = float(1.0 / std::sqrt(double(g.Dh)));
-  dim3 grid((M + 63) / 64, g.H);
-  hipLaunchKernelGGL(k_attn_f32<64>, grid, dim3(64), 0, s, qk, vt, ldv, out, M, g.d, scale);
-  DC_HIP(hipGetLastError());
-  return Status::ok();
 }
 
 }  // namespace dc

@@ -6,7 +6,7 @@
 //   * LayerNorm with modulation: y = (x - mu) r, r = (var + eps)^-1/2,
 //     dy = r (dxc - y mean(y dxc)), dxc = dx - mean(dx); a = y (1 + s) + sh, da = dy (1 + s);
 //   * softmax attention per head, s = q.k c, ds = (dq.k + q.dk) c (c = 1/sqrt(d_h)):
-//     o = sum_j P_j v_j, do = sum_j P_j (ds_j - sum_i P_i ds_i) v_j + P_j dv_j;
+//     o = sum_j P_j v_j, do = sum_j P_j (ds_j - sum_i P_i ds_i) v_j + P_j dv_j (attention_f32.hip);
 //   * GELU-tanh: g = z/2 (1 + tanh u), u = sqrt(2/pi)(z + 0.044715 z^3),
 //     dg = (1/2 (1 + tanh u) + z/2 (1 - tanh^2 u) sqrt(2/pi)(1 + 3 0.044715 z^2)) dz.
 // Plus a fixed-order sum-of-squares reduction (the L2 norms of Eq. 5 and Eq. 7) and a
@@ -70,72 +70,6 @@ __global__ void __launch_bounds__(kRowThreads) k_ln_mod_jvp(const float* __restr
     const double f = 1.0 + double(scale[c]);
     a[base + c] = float(y * f + double(shift[c]));
     da[base + c] = float(dy * f);
-  }
-}
-
-// one thread per (query, head, half of the head's dimensions): keys streamed through LDS
-// in tiles of 32, the unnormalised sums rescaled online when the running maximum grows.
-// qkv, dqkv: [M, 3d] (Q | K | V, head-major columns); o, dout: [M, d].
-constexpr int kDh = 64, kHalf = 32, kKT = 32;
-__global__ void __launch_bounds__(128) k_attn_jvp_f32(const float* __restrict__ qkv,
-                                                      const float* __restrict__ dqkv, int M, int d,
-                                                      float scale, float* __restrict__ o,
-                                                      float* __restrict__ dout) {
-  __shared__ float sK[kKT][kDh + 1], sdK[kKT][kDh + 1], sV[kKT][kDh + 1], sdV[kKT][kDh + 1];
-  const int head = blockIdx.y;
-  const int qi = threadIdx.x & 63, half = threadIdx.x >> 6;
-  const int qrow = blockIdx.x * 64 + qi;
-  const int ld = 3 * d;
-  float qv[kDh], dq[kDh];
-  for (int i = 0; i < kDh; ++i) {
-    const size_t e = size_t(min(qrow, M - 1)) * ld + head * kDh + i;
-    qv[i] = qkv[e];
-    dq[i] = dqkv[e];
-  }
-  float A[kHalf], B[kHalf], Dv[kHalf];
-  for (int i = 0; i < kHalf; ++i) A[i] = B[i] = Dv[i] = 0.f;
-  float m = -INFINITY, l = 0.f, cs = 0.f;
-  for (int k0 = 0; k0 < M; k0 += kKT) {
-    for (int e = threadIdx.x; e < kKT * kDh; e += 128) {
-      const int r = e / kDh, c = e % kDh;
-      const int key = k0 + r;
-      const bool ok = key < M;
-      const size_t b = size_t(ok ? key : 0) * ld + head * kDh + c;
-      sK[r][c] = ok ? qkv[b + d] : 0.f;
-      sdK[r][c] = ok ? dqkv[b + d] : 0.f;
-      sV[r][c] = ok ? qkv[b + 2 * d] : 0.f;
-      sdV[r][c] = ok ? dqkv[b + 2 * d] : 0.f;
-    }
-    __syncthreads();
-    const int n = min(kKT, M - k0);
-    for (int j = 0; j < n; ++j) {
-      float s = 0.f, ds = 0.f;
-      for (int i = 0; i < kDh; ++i) {
-        s += qv[i] * sK[j][i];
-        ds += dq[i] * sK[j][i] + qv[i] * sdK[j][i];
-      }
-      s *= scale;
-      ds *= scale;
-      const float mn = fmaxf(m, s);
-      const float al = expf(m - mn), p = expf(s - mn);
-      l = l * al + p;
-      cs = cs * al + p * ds;
-      for (int i = 0; i < kHalf; ++i) {
-        const int c = half * kHalf + i;
-        B[i] = B[i] * al + p * sV[j][c];
-        A[i] = A[i] * al + p * ds * sV[j][c];
-        Dv[i] = Dv[i] * al + p * sdV[j][c];
-      }
-      m = mn;
-    }
-    __syncthreads();
-  }
-  if (qrow >= M) return;
-  const float inv = 1.0f / l, c = cs * inv;
-  for (int i = 0; i < kHalf; ++i) {
-    const size_t e = size_t(qrow) * d + head * kDh + half * kHalf + i;
-    o[e] = B[i] * inv;
-    dout[e] = (A[i] - c * B[i] + Dv[i]) * inv;
   }
 }
 
@@ -205,16 +139,6 @@ Status ln_mod_jvp(const float* x, const float* dx, int rows, int ld, int d, cons
   if (rows <= 0) return Status::ok();
   hipLaunchKernelGGL(k_ln_mod_jvp, dim3(rows), dim3(kRowThreads), 0, s, x, dx, ld, d, shift, scale, a,
                      da, eps);
-  DC_HIP(hipGetLastError());
-  return Status::ok();
-}
-
-Status attention_jvp_f32(const float* qkv, const float* dqkv, const Geo& g, int M, float* o,
-                         float* dout, hipStream_t s) {
-  if (g.Dh != kDh) return Status::shape("calibration attention tangent supports head_dim 64");
-  const float scale = float(1.0 / std::sqrt(double(g.Dh)));
-  hipLaunchKernelGGL(k_attn_jvp_f32, dim3((M + 63) / 64, g.H), dim3(128), 0, s, qkv, dqkv, M, g.d, scale,
-                     o, dout);
   DC_HIP(hipGetLastError());
   return Status::ok();
 }

@@ -141,14 +141,6 @@ struct EpiQKVBf16 {
     else vt[size_t(n - 2 * d) * ldv + m] = to_bf16(v);
   }
 };
-struct EpiQKVF32 {
-  const float* bias; float* qk; float* vt; int d; int ldv;
-  __device__ void operator()(int m, int n, float v) const {
-    v += bias[n];
-    if (n < 2 * d) qk[size_t(m) * 2 * d + n] = v;
-    else vt[size_t(n - 2 * d) * ldv + m] = v;
-  }
-};
 struct EpiGateResidual {
   const float* bias; const float* gate; float* h; int ldh;
   static constexpr int kRowVec = 4;
@@ -757,11 +749,6 @@ Status gemm_f32_head(const float* A, int lda, const float* W, const float* bias,
                      float dsigma, const Geo& g, int M, hipStream_t s) {
   EpiHeadEuler e{bias, x, dsigma, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp};
   return launch_f32(A, lda, W, g.d, M, g.P, g.d, e, s);
-}
-
-Status gemm_f32_qkv(const float* A, const float* W, const float* bias, float* qk, float* vt,
-                    int ldv, const Geo& g, int M, hipStream_t s) {
-  return launch_f32(A, g.d, W, g.d, M, 3 * g.d, g.d, EpiQKVF32{bias, qk, vt, g.d, ldv}, s);
 }
 
 Status gemm_bf16_qkv(const uint16_t* A, const uint16_t* W, const float* bias, uint16_t* qk,

@@ -102,6 +102,9 @@ Workspace workspace_layout(const Geo& g, int batch);
 
 constexpr int kDriftBlocks = 1024;  // fixed grid per sample: reproducible reductions
 
+// Compute units of the current device (looked up once per device); 0 if there is none.
+int compute_units();
+
 // ---------------------------------------------------------------------------
 // kernel launchers (kernels_*.hip, gemm.hip, attention.hip)
 // ---------------------------------------------------------------------------
@@ -119,8 +122,6 @@ Status gemm_f32_patch_embed(const float* A, const float* W, const float* bias, c
                             bool pos_bf16, float* out, int ldo, int M, int N, hipStream_t s);
 Status gemm_f32_head(const float* A, int lda, const float* W, const float* bias, float* x,
                      float dsigma, const Geo& g, int M, hipStream_t s);
-Status gemm_f32_qkv(const float* A, const float* W, const float* bias, float* qk, float* vt,
-                    int ldv, const Geo& g, int M, hipStream_t s);
 // the same fp32 SIMT GEMMs with bf16 weights (bits widened exactly on load): the tangent
 // passes of the calibration on bf16 models
 Status gemm_f32_bias_act(const float* A, int lda, const uint16_t* W, int ldw, const float* bias,
@@ -158,8 +159,8 @@ Status head_euler_bf16(const float* gin, const uint16_t* resid, const uint16_t* 
 // with too little scratch the tail is not split.
 Status attention_bf16(const uint16_t* qk, const uint16_t* vt, int ldv, uint16_t* out,
                       const Geo& g, int M, float* part, size_t part_bytes, hipStream_t s);
-Status attention_f32(const float* qk, const float* vt, int ldv, float* out, const Geo& g, int M,
-                     hipStream_t s);
+// fp32 attention over qkv [M, 3d] (Q | K | V), out [M, d] (attention_f32.hip).
+Status attention_f32(const float* qkv, float* out, const Geo& g, int M, hipStream_t s);
 
 // Elementwise / row kernels.
 Status ln_modulate(const float* x, int rows, int ldx, const float* shift, const float* scale,

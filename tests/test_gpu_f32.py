@@ -1,0 +1,77 @@
+"""The fp32 model's kernels at the edges of their dispatch, against the oracle.
+
+Token counts around the 16-query and 32-key tiles (1 token; one short of, at and one past a
+tile), and counts that select each split of the attention on 256 compute units: eight waves
+per 16 queries (one round of workgroups), four waves (five rounds of 16 queries against
+three of 32), 32 queries per workgroup (two rounds against one)."""
+import numpy as np
+import pytest
+
+from oracle import calibrate as cal
+from oracle import dit
+from paper_2608_16354_amd import inputs as I
+from tests.gpu_util import mod_input, rel_l2, say, t
+from tests.test_gpu_kernels import _OneBlock
+
+pytestmark = pytest.mark.gpu
+
+
+def _shape(d, lat, n_txt, n_blocks=1):
+    return I.ModelShape(n_blocks=n_blocks, hidden=d, heads=d // 64, head_dim=64, mlp_hidden=4 * d, lat_c=16,
+                        lat_t=lat[0], lat_h=lat[1], lat_w=lat[2], patch=2, n_txt=n_txt, dtype="f32")
+
+
+@pytest.fixture(scope="module")
+def api():
+    from paper_2608_16354_amd import api as A
+    A.L.load()
+    return A
+
+
+SHAPES = {
+    "N1": _shape(128, (1, 2, 2), 0),
+    "N15": _shape(128, (3, 2, 10), 0),
+    "N16": _shape(256, (1, 8, 8), 0),
+    "N33": _shape(256, (2, 8, 8), 1),
+    "N257": _shape(384, (4, 16, 16), 1),
+    "N1001-h8": _shape(512, (7, 22, 26), 0),
+    "N1429-h12": _shape(768, (4, 38, 36), 61),
+}
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_block_forward_f32(api, dev, name):
+    import torch
+    m = SHAPES[name]
+    W = I.Weights(m, 120)
+    dm = api.DeviceModel(_OneBlock(W, 0), dev)
+    ws = api.Workspace(m, 1, dev)
+    h = I.hidden_state(m, (50,))
+    mod = mod_input(m, (51,))
+    dh = t(h[None], dev)
+    say("f32 block_forward", name, "N =", m.n_tok)
+    api.dc_block_forward(dm, 0, t(mod, dev), dh, [0], ws)
+    torch.cuda.synchronize()
+    got = dh[0].cpu().numpy()
+    want = dit.block(dit.Params(W), 0, mod.astype(np.float64), h.astype(np.float64))
+    err_h, err_d = rel_l2(got, want), rel_l2(got - h, want - h)
+    say(name, "block rel-L2 h_out", err_h, "update", err_d)
+    # fp32 sums of up to 4 d = 3,072 terms: about sqrt(3072) 2^-24 = 3.3e-6 at worst
+    assert err_h < 4e-6 and err_d < 4e-6
+
+
+@pytest.mark.parametrize("lat,n_txt", [((1, 6, 10), 0), ((3, 10, 12), 5)])
+def test_calibration_at_ragged_token_counts(api, dev, lat, n_txt):
+    """15 tokens (less than one tile) and 95 (ragged), one refresh of each run length."""
+    import torch
+    m = _shape(256, lat, n_txt, n_blocks=2)
+    W = I.Weights(m, 121)
+    K, h_max = 4, 2
+    x1, txt = I.latent(m, 121, 0), I.text(m, 121, 0)
+    say("calibration N =", m.n_tok)
+    q, d = api.dc_calibrate_tables(api.DeviceModel(W, dev), torch.from_numpy(x1).to(dev),
+                                   torch.from_numpy(txt).to(dev), I.sigmas(K), h_max, 1e-6)
+    tr = cal.Trace(dit.Params(W), x1.astype(np.float64), txt.astype(np.float64), I.sigmas(K))
+    qo, do = cal.run_tables(tr, h_max, 1e-6)
+    assert np.array_equal(q == 0.0, qo == 0.0) and np.array_equal(d == 0.0, do == 0.0)
+    assert np.allclose(q, qo, rtol=1e-5) and np.allclose(d, do, rtol=1e-6)
