@@ -169,7 +169,8 @@ Status patch_embed(const Geo& g, const dc_model_weights* w, const float* x, cons
                               hb, g, s));
     } else {
       DC_TRY(patchify(x + size_t(b) * lat, patches, g, s));
-      DC_TRY(gemm_f32_patch_embed(patches, w->w_pe, w->b_pe, w->pos, false, hb, g.d, g.Nv, g.d, s));
+      DC_TRY(gemm_f32_patch_embed(patches, w->w_pe, w->b_pe, static_cast<const float*>(w->pos), hb, g.d, g.Nv,
+                                  g.d, s));
     }
     if (g.Nt > 0) DC_TRY(copy_text(txt + size_t(b) * g.Nt * g.d, hb, g, s));
   }

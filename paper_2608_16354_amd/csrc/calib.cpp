@@ -14,7 +14,7 @@
 //          x_k (a Jacobian-vector product: the network run in tangent mode).
 // Runs with j + h > K price nothing and stay 0.  The trace runs the library's own
 // kernels for the model's dtype (bf16 models: bf16 MFMA blocks); r, u, the perturbations
-// and every tangent are fp32 (fp32 SIMT kernels, calib.hip, with bf16 weights widened
+// and every tangent are fp32 (calib.hip and the fp32 GEMMs, with bf16 weights widened
 // exactly on load).
 #include <algorithm>
 #include <cmath>
@@ -138,7 +138,7 @@ struct Calib {
                       nullptr);
   }
 
-  // the fp32 SIMT GEMMs with the model's weights (fp32, or bf16 widened on load)
+  // the fp32 GEMMs with the model's weights (fp32, or bf16 widened on load)
   Status mm(const float* A, int lda, const void* W, int ldw, const float* bias, float* out, int ldo,
             int M, int N, int Kd) const {
     if (g.bf16)

@@ -1,4 +1,4 @@
-// GEMMs of the denoising step: C = A W^T with fused epilogues.
+// bf16 GEMMs of the denoising step: C = A W^T with fused epilogues.
 //
 // bf16 block GEMMs (QKV, out-projection, MLP up / down): v_mfma_f32_32x32x16_bf16,
 // 8 waves, block tile 384 x 192 x 64 (QKV, out-projection, MLP down: fewer operand
@@ -12,8 +12,7 @@
 // the same LDS-DMA GEMM with a 64 x 64 tile (N = 64 outputs) and the unpatchify +
 // Euler epilogue, after LN-modulation to bf16 rows.
 // bf16 patch embedding: fp32-accurate split-bf16 MFMA with the patchify gather fused.
-// f32 path: a plain SIMT tiled kernel for the fp32 model and the small fp32
-// GEMMs (patch embedding of the fp32 model, timestep MLP).
+// (fp32 GEMMs: gemm_f32.hip.)
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -62,10 +61,9 @@ __device__ inline float gelu_tanh_fast(float z) {
   const float y = 0.7978845608028654f * (z + 0.044715f * z * z * z);
   return z * __builtin_amdgcn_rcpf(1.0f + __expf(-2.0f * y));
 }
-__device__ inline float silu(float z) { return z / (1.0f + expf(-z)); }
 
 // ---------------------------------------------------------------------------
-// epilogues: operator()(m, n, acc) for one output element
+// epilogues
 // ---------------------------------------------------------------------------
 // The MFMA GEMM hands its epilogue either one accumulator column at a time: col(mb,
 // n, M, v) gets v[i] = C[mb + 8 (i / 4) + i % 4][n] for i < 16 (mb a multiple of 4),
@@ -134,12 +132,6 @@ struct EpiQKVBf16 {
       }
     }
   }
-  __device__ void operator()(int m, int n, float v) const {
-    v += bias[n];
-    if (n < d) qk[size_t(m) * 2 * d + n] = to_bf16(v * qscale);
-    else if (n < 2 * d) qk[size_t(m) * 2 * d + n] = to_bf16(v);
-    else vt[size_t(n - 2 * d) * ldv + m] = to_bf16(v);
-  }
 };
 struct EpiGateResidual {
   const float* bias; const float* gate; float* h; int ldh;
@@ -185,10 +177,6 @@ struct EpiGateResidual {
     for (int i = 0; i < 16; ++i)
       if (mb + 8 * (i >> 2) + (i & 3) < M) p[size_t(8 * (i >> 2) + (i & 3)) * ldh] = old[i] + g * (v[i] + b);
   }
-  __device__ void operator()(int m, int n, float v) const {
-    float* p = h + size_t(m) * ldh + n;
-    *p = *p + gate[n] * (v + bias[n]);
-  }
 };
 struct EpiGeluBf16 {
   const float* bias; uint16_t* out; int ldo;
@@ -221,30 +209,6 @@ struct EpiGeluBf16 {
       for (int i = 0; i < 16; ++i)
         if (mb + 8 * (i >> 2) + (i & 3) < M) o[size_t(8 * (i >> 2) + (i & 3)) * ldo] = to_bf16(gelu_tanh(v[i] + b));
     }
-  }
-  __device__ void operator()(int m, int n, float v) const {
-    out[size_t(m) * ldo + n] = to_bf16(gelu_tanh(v + bias[n]));
-  }
-};
-struct EpiGeluF32 {
-  const float* bias; float* out; int ldo;
-  __device__ void operator()(int m, int n, float v) const {
-    out[size_t(m) * ldo + n] = gelu_tanh(v + bias[n]);
-  }
-};
-struct EpiBiasAct {
-  const float* bias; float* out; int ldo; int act;
-  __device__ void operator()(int m, int n, float v) const {
-    v += bias[n];
-    out[size_t(m) * ldo + n] = act ? silu(v) : v;
-  }
-};
-struct EpiPatch {
-  const float* bias; const float* pos_f; const uint16_t* pos_b; float* out; int ldo;
-  __device__ void operator()(int m, int n, float v) const {
-    const size_t e = size_t(m) * ldo + n;
-    const float p = pos_b ? from_bf16(pos_b[e]) : pos_f[e];
-    out[e] = (v + bias[n]) + p;
   }
 };
 // Head + Euler: token m, patch-vector index n -> latent element; x += dsigma * (acc + b).
@@ -279,13 +243,6 @@ struct EpiHeadEuler {
 #pragma unroll
     for (int i = 0; i < 16; ++i)
       if (mb + 8 * (i >> 2) + (i & 3) < M) *dst[i] = old[i] + dsigma * (v[i] + bn);
-  }
-  __device__ void operator()(int m, int n, float v) const {
-    const int pp = p * p;
-    const int c = n / pp, a = (n / p) % p, b = n % p;
-    const int t = m / (Hp * Wp), i = (m / Wp) % Hp, j = m % Wp;
-    float* dst = x + ((size_t(c) * T + t) * Hl + (p * i + a)) * Wl + (p * j + b);
-    *dst = *dst + dsigma * (v + bias[n]);
   }
 };
 
@@ -634,123 +591,11 @@ __global__ void __launch_bounds__(512) k_patch_embed_bf16(const float* __restric
   }
 }
 
-// ---------------------------------------------------------------------------
-// fp32 SIMT GEMM: 64x64 tile, k-step 16, each thread a 4x4 block of outputs
-// ---------------------------------------------------------------------------
-// four consecutive weights as fp32 (W in fp32, or bf16 bits widened exactly)
-__device__ inline float4 load_w4(const float* W, size_t e) { return *reinterpret_cast<const float4*>(W + e); }
-__device__ inline float4 load_w4(const uint16_t* W, size_t e) {
-  const uint2 u = *reinterpret_cast<const uint2*>(W + e);
-  return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
-                     __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u));
-}
-
-template <class Epi, class WT>
-__global__ void __launch_bounds__(256) k_gemm_f32(const float* __restrict__ A, int lda,
-                                                  const WT* __restrict__ W, int ldw, int M,
-                                                  int N, int K, Epi epi) {
-  __shared__ float sA[16][64 + 4];
-  __shared__ float sW[16][64 + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    const int gm = m0 + lr, gn = n0 + lr;
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), w = a;
-    if (gm < M) a = *reinterpret_cast<const float4*>(A + size_t(gm) * lda + k0 + lk);
-    if (gn < N) w = load_w4(W, size_t(gn) * ldw + k0 + lk);
-    sA[lk + 0][lr] = a.x; sA[lk + 1][lr] = a.y; sA[lk + 2][lr] = a.z; sA[lk + 3][lr] = a.w;
-    sW[lk + 0][lr] = w.x; sW[lk + 1][lr] = w.y; sW[lk + 2][lr] = w.z; sW[lk + 3][lr] = w.w;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float av[4], wv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = sA[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wv[j] = sW[k][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += av[i] * wv[j];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx + 16 * j;
-      if (m < M && n < N) epi(m, n, acc[i][j]);
-    }
-}
-
-template <class Epi, class WT>
-Status launch_f32(const float* A, int lda, const WT* W, int ldw, int M, int N, int K,
-                  const Epi& epi, hipStream_t s) {
-  if (M <= 0 || N <= 0) return Status::ok();
-  if (K % 16 || lda % 4 || ldw % 4) return Status::shape("f32 GEMM needs K % 16 == 0, aligned rows");
-  dim3 grid((N + 63) / 64, (M + 63) / 64);
-  hipLaunchKernelGGL((k_gemm_f32<Epi, WT>), grid, dim3(256), 0, s, A, lda, W, ldw, M, N, K, epi);
-  DC_HIP(hipGetLastError());
-  return Status::ok();
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
 // entry points
 // ---------------------------------------------------------------------------
-Status gemm_f32_bias_act(const float* A, int lda, const float* W, int ldw, const float* bias,
-                         float* out, int ldo, int M, int N, int K, Act act, hipStream_t s) {
-  return launch_f32(A, lda, W, ldw, M, N, K, EpiBiasAct{bias, out, ldo, act == Act::kSilu ? 1 : 0}, s);
-}
-
-Status gemm_f32_gate_residual(const float* A, int lda, const float* W, int ldw, const float* bias,
-                              const float* gate, float* h, int ldh, int M, int N, int K,
-                              hipStream_t s) {
-  return launch_f32(A, lda, W, ldw, M, N, K, EpiGateResidual{bias, gate, h, ldh}, s);
-}
-
-Status gemm_f32_bias_act(const float* A, int lda, const uint16_t* W, int ldw, const float* bias,
-                         float* out, int ldo, int M, int N, int K, Act act, hipStream_t s) {
-  if (ldw % 4) return Status::shape("f32 GEMM with bf16 weights needs ldw % 4 == 0");
-  return launch_f32(A, lda, W, ldw, M, N, K, EpiBiasAct{bias, out, ldo, act == Act::kSilu ? 1 : 0}, s);
-}
-
-Status gemm_f32_gate_residual(const float* A, int lda, const uint16_t* W, int ldw, const float* bias,
-                              const float* gate, float* h, int ldh, int M, int N, int K,
-                              hipStream_t s) {
-  if (ldw % 4) return Status::shape("f32 GEMM with bf16 weights needs ldw % 4 == 0");
-  return launch_f32(A, lda, W, ldw, M, N, K, EpiGateResidual{bias, gate, h, ldh}, s);
-}
-
-Status gemm_f32_head(const float* A, int lda, const uint16_t* W, const float* bias, float* x,
-                     float dsigma, const Geo& g, int M, hipStream_t s) {
-  EpiHeadEuler e{bias, x, dsigma, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp};
-  return launch_f32(A, lda, W, g.d, M, g.P, g.d, e, s);
-}
-
-Status gemm_f32_gelu(const float* A, int lda, const float* W, int ldw, const float* bias,
-                     float* out, int ldo, int M, int N, int K, hipStream_t s) {
-  return launch_f32(A, lda, W, ldw, M, N, K, EpiGeluF32{bias, out, ldo}, s);
-}
-
-Status gemm_f32_patch_embed(const float* A, const float* W, const float* bias, const void* pos,
-                            bool pos_bf16, float* out, int ldo, int M, int N, hipStream_t s) {
-  EpiPatch e{bias, pos_bf16 ? nullptr : static_cast<const float*>(pos),
-             pos_bf16 ? static_cast<const uint16_t*>(pos) : nullptr, out, ldo};
-  return launch_f32(A, 64, W, 64, M, N, 64, e, s);
-}
-
-Status gemm_f32_head(const float* A, int lda, const float* W, const float* bias, float* x,
-                     float dsigma, const Geo& g, int M, hipStream_t s) {
-  EpiHeadEuler e{bias, x, dsigma, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp};
-  return launch_f32(A, lda, W, g.d, M, g.P, g.d, e, s);
-}
-
 Status gemm_bf16_qkv(const uint16_t* A, const uint16_t* W, const float* bias, uint16_t* qk,
                      uint16_t* vt, int ldv, const Geo& g, int M, hipStream_t s) {
   return launch_dma<384, 192, 4, 2, 2>(A, g.d, W, g.d, M, 3 * g.d, g.d,

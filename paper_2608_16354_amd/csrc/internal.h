@@ -110,7 +110,7 @@ int compute_units();
 // ---------------------------------------------------------------------------
 enum class Act { kNone, kSilu };
 
-// fp32 GEMM, C = A W^T (+ epilogue).  A [M, K] (lda), W [N, K] (ldw).
+// fp32 GEMM, C = A W^T (+ epilogue).  A [M, K] (lda), W [N, K] (ldw); K % 64 == 0.
 Status gemm_f32_bias_act(const float* A, int lda, const float* W, int ldw, const float* bias,
                          float* out, int ldo, int M, int N, int K, Act act, hipStream_t s);
 Status gemm_f32_gate_residual(const float* A, int lda, const float* W, int ldw, const float* bias,
@@ -118,11 +118,11 @@ Status gemm_f32_gate_residual(const float* A, int lda, const float* W, int ldw, 
                               hipStream_t s);
 Status gemm_f32_gelu(const float* A, int lda, const float* W, int ldw, const float* bias,
                      float* out, int ldo, int M, int N, int K, hipStream_t s);
-Status gemm_f32_patch_embed(const float* A, const float* W, const float* bias, const void* pos,
-                            bool pos_bf16, float* out, int ldo, int M, int N, hipStream_t s);
+Status gemm_f32_patch_embed(const float* A, const float* W, const float* bias, const float* pos,
+                            float* out, int ldo, int M, int N, hipStream_t s);
 Status gemm_f32_head(const float* A, int lda, const float* W, const float* bias, float* x,
                      float dsigma, const Geo& g, int M, hipStream_t s);
-// the same fp32 SIMT GEMMs with bf16 weights (bits widened exactly on load): the tangent
+// the same fp32 GEMMs with bf16 weights (bits widened exactly on load): the tangent
 // passes of the calibration on bf16 models
 Status gemm_f32_bias_act(const float* A, int lda, const uint16_t* W, int ldw, const float* bias,
                          float* out, int ldo, int M, int N, int K, Act act, hipStream_t s);

@@ -75,3 +75,24 @@ def test_calibration_at_ragged_token_counts(api, dev, lat, n_txt):
     qo, do = cal.run_tables(tr, h_max, 1e-6)
     assert np.array_equal(q == 0.0, qo == 0.0) and np.array_equal(d == 0.0, do == 0.0)
     assert np.allclose(q, qo, rtol=1e-5) and np.allclose(d, do, rtol=1e-6)
+
+
+@pytest.mark.parametrize("d,K", [(256, 1), (256, 17), (384, 40), (1024, 50), (768, 100), (128, 130)])
+def test_time_modulation_tiles(api, dev, d, K):
+    """Step counts and widths that select each fp32 GEMM tile of the modulation: 32 x 16 (few
+    columns), 64 x 48 for 33 to 128 steps and many columns, 32 x 32; ragged step counts."""
+    import torch
+    m = _shape(d, (1, 4, 4), 0)
+    W = I.Weights(m, 122)
+    sig = np.linspace(1.0, 0.02, K)
+    mod = torch.zeros((K, m.n_blocks + 1, 6, d), device=dev)
+    say("time_modulation d =", d, "K =", K)
+    api.dc_time_modulation(api.DeviceModel(W, dev), sig, mod, api.Workspace(m, 1, dev))
+    torch.cuda.synchronize()
+    got = mod.cpu().numpy()
+    P = dit.Params(W)
+    for k in {0, 15, 16, 31, 32, K // 2, K - 1} & set(range(K)):
+        blocks, head = dit.step_modulation(P, sig[k])
+        assert rel_l2(got[k, 0], blocks[0]) < 1e-5
+        assert rel_l2(got[k, 1, :2], head) < 1e-5
+        assert not got[k, 1, 2:].any()
