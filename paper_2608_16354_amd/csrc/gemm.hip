@@ -1,13 +1,11 @@
 // bf16 GEMMs of the denoising step: C = A W^T with fused epilogues.
 //
-// bf16 block GEMMs (QKV, out-projection, MLP up / down): v_mfma_f32_32x32x16_bf16,
-// 8 waves, block tile 384 x 192 x 64 (QKV, out-projection, MLP down: fewer operand
-// lines per FLOP, the L1 miss queue being the limit) or 320 x 256 x 64 (MLP up: still
-// fewer lines per FLOP, and its 30 column tiles quantise well over the rounds), tiles
-// fed global -> LDS by LDS-DMA into two
-// stages (the refill of the next k-step interleaved with this k-step's MFMAs),
-// XOR-swizzled 128-byte rows, one barrier per k-step, XCD-aware tile order;
-// epilogues take one accumulator column at a time.
+// bf16 block GEMMs (QKV, out-projection, MLP up / down): v_mfma_f32_32x32x16_bf16, tiles
+// fed global -> LDS by LDS-DMA, XOR-swizzled 128-byte rows, k-steps of 64, one barrier per
+// k-step, XCD-aware tile order; epilogues take one accumulator column at a time.  Six tile
+// shapes, chosen per call by a cost model (block_gemm): long sequences take 384 x 192 or 320 x 256
+// (fewest operand lines per FLOP, the L1 miss queue being the limit there), short ones the
+// smaller tiles that spread over all compute units.
 // bf16 head + Euler for models wider than the one-pass head kernel takes (d > 2048):
 // the same LDS-DMA GEMM with a 64 x 64 tile (N = 64 outputs) and the unpatchify +
 // Euler epilogue, after LN-modulation to bf16 rows.
@@ -247,13 +245,12 @@ struct EpiHeadEuler {
 };
 
 // ---------------------------------------------------------------------------
-// bf16 MFMA GEMM, LDS-DMA pipeline.  512 threads = 8 waves (2 per SIMD), block
-// tile BM x BN x 64.  Tiles go global -> LDS with global_load_lds_dwordx4 (lane i
+// bf16 MFMA GEMM, LDS-DMA pipeline.  WM x WN waves, block tile BM x BN x 64.  Tiles go global -> LDS with global_load_lds_dwordx4 (lane i
 // of an instruction lands at LDS base + 16 i, so the XOR swizzle is applied to the
 // global address each lane fetches): no staging registers and no LDS write
-// instructions.  Two stages, one barrier per k-step: the loads for step k+1 are
+// instructions.  ST stages, one barrier per k-step: the loads for step k + ST - 1 are
 // issued among the MFMAs of the first DS 16-wide k-slices of step k (the block
-// GEMMs use DS = 2, so the last refill has half a step to land).  Rows past M or N
+// GEMMs use DS = 2, so with two stages the last refill has half a step to land).  Rows past M or N
 // are clamped to the last row (their results are never stored).  Workgroups are
 // renumbered so that each XCD (assigned round-robin by workgroup id) processes a
 // contiguous range of tiles.
@@ -328,7 +325,7 @@ __device__ inline void gemm_epilogue(f32x16 (&acc)[TM][TN], uint4* lds, int m0, 
   }
 }
 
-template <int BM, int BN, int WM, int WN, int DS, class Epi>
+template <int BM, int BN, int WM, int WN, int DS, int ST, class Epi>
 __global__ void __launch_bounds__(WM * WN * 64) k_gemm_dma(const uint16_t* __restrict__ A, int lda,
                                                   const uint16_t* __restrict__ W, int ldw, int M,
                                                   int N, int K, int tiles_n, int tiles, int per_xcd,
@@ -341,11 +338,8 @@ __global__ void __launch_bounds__(WM * WN * 64) k_gemm_dma(const uint16_t* __res
   static_assert(TM >= 1 && TN >= 1 && AI * NW * 64 == BM * 8 && BI * NW * 64 == BN * 8,
                 "tile shape");
   // one array, so every stage address is a constant offset from one base
-  __shared__ uint4 lds[2 * (BM + BN) * 8];
-  uint4* const sA0 = lds;
-  uint4* const sB0 = lds + BM * 8;
-  uint4* const sA1 = lds + (BM + BN) * 8;
-  uint4* const sB1 = lds + (2 * BM + BN) * 8;
+  constexpr int STAGE = (BM + BN) * 8;
+  __shared__ uint4 lds[ST * STAGE];
 
   const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (t >= tiles) return;
@@ -386,14 +380,15 @@ __global__ void __launch_bounds__(WM * WN * 64) k_gemm_dma(const uint16_t* __res
   const int KT = K / BK;                         // even: the launcher requires K % 128 == 0
 
   const int r32 = lane & 31, hi = lane >> 5;
-  // one DMA instruction (j < AI + BI) of the refill of stage (da, db) with k-step kt;
+  // one DMA instruction (j < AI + BI) of the refill of stage `to` with k-step kt;
   // compute() spreads the refill over its first DS k-slices
-  auto dma_one = [&](uint4* da, uint4* db, int kt, int j) {
+  auto dma_one = [&](uint4* to, int kt, int j) {
     const int k0 = kt * BK;
-    if (j < AI) dma16(A + k0, offA[j], da + (wave * AI + j) * 64);
-    else dma16(W + k0, offB[j - AI], db + (wave * BI + (j - AI)) * 64);
+    if (j < AI) dma16(A + k0, offA[j], to + (wave * AI + j) * 64);
+    else dma16(W + k0, offB[j - AI], to + BM * 8 + (wave * BI + (j - AI)) * 64);
   };
-  auto compute = [&](const uint4* sa, const uint4* sb, uint4* da, uint4* db, int kt) {
+  auto compute = [&](const uint4* sa, uint4* to, int kt) {
+    const uint4* sb = sa + BM * 8;
 #pragma unroll
     for (int kk = 0; kk < BK / 16; ++kk) {
       if (kt >= 0) {
@@ -401,7 +396,7 @@ __global__ void __launch_bounds__(WM * WN * 64) k_gemm_dma(const uint16_t* __res
         constexpr int DPS = (AI + BI + DS - 1) / DS;
 #pragma unroll
         for (int j = kk * DPS; j < (kk + 1) * DPS; ++j)
-          if (j < AI + BI && kk < DS) dma_one(da, db, kt, j);
+          if (j < AI + BI && kk < DS) dma_one(to, kt, j);
       }
       const int ch = kk * 2 + hi;
       bf16x8 af[TM], bf[TN];
@@ -424,41 +419,224 @@ __global__ void __launch_bounds__(WM * WN * 64) k_gemm_dma(const uint16_t* __res
   };
 
 #pragma unroll
-  for (int j = 0; j < AI + BI; ++j) dma_one(sA0, sB0, 0, j);
-  // before each barrier: this wave's refill has landed
-  for (int kt = 0; kt < KT; kt += 2) {
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    compute(sA0, sB0, sA1, sB1, kt + 1);
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    compute(sA1, sB1, sA0, sB0, kt + 2 < KT ? kt + 2 : -1);
+  for (int i = 0; i < ST - 1; ++i)
+    if (i < KT)
+#pragma unroll
+      for (int j = 0; j < AI + BI; ++j) dma_one(lds + i * STAGE, i, j);
+  for (int kt0 = 0; kt0 < KT; kt0 += ST) {
+#pragma unroll
+    for (int i = 0; i < ST; ++i) {
+      const int kt = kt0 + i;
+      if (kt >= KT) break;
+      // before the barrier: this wave's part of k-step kt has landed (the ST - 2 steps after
+      // it may still be in flight)
+      if (ST > 2 && kt + ST - 2 < KT) wait_vmcnt<(ST - 2) * (AI + BI)>();
+      else wait_vmcnt<0>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      compute(lds + i * STAGE, lds + (i + ST - 1) % ST * STAGE, kt + ST - 1 < KT ? kt + ST - 1 : -1);
+    }
   }
 
   static_assert(Epi::kRowVec == 0 || sizeof(lds) >= NW * 32 * kEpiStride * sizeof(float), "epilogue LDS");
   gemm_epilogue<BM, BN, WM, WN>(acc, lds, m0, n0, M, N, wave, lane, rows_ok, epi);
 }
 
-template <int BM, int BN, int WM, int WN, int DS, class Epi>
-Status launch_dma(const uint16_t* A, int lda, const uint16_t* W, int ldw, int M, int N, int K,
-                  const Epi& epi, hipStream_t s) {
-  if (M <= 0) return Status::ok();
+// 128 x 128 tile for the middle sizes (8 waves of 64 x 32).  A tile this small has little
+// MFMA work per k-step (512 cycles), so the LDS latency after each barrier shows: here the
+// fragments of the next k-slice, across the barrier too, are read while this slice
+// multiplies.  For that a k-step has to have landed one barrier before it is multiplied,
+// hence four stages of 32 KB.  120 k-steps on 195 tiles: 53.8 us, 60.0 with k_gemm_dma (the
+// fill of 32 KB per k-step and compute unit is the rest: about 38 of 64 bytes per cycle).
+template <class Epi>
+__global__ void __launch_bounds__(512) k_gemm_pipe(const uint16_t* __restrict__ A, int lda,
+                                                   const uint16_t* __restrict__ W, int ldw, int M,
+                                                   int N, int K, int tiles_n, int tiles, int per_xcd,
+                                                   int rows_ok, Epi epi) {
+  constexpr int BM = 128, BN = 128, WM = 2, WN = 4, ST = 4, BK = 64, NW = WM * WN;
+  constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
+  constexpr int AI = BM * 8 / 64 / NW, BI = BN * 8 / 64 / NW;     // DMA instructions per wave
+  static_assert(AI + BI == 4, "one DMA instruction per k-slice");
+  constexpr int STAGE = (BM + BN) * 8;
+  __shared__ uint4 lds[ST * STAGE];
+  const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (t >= tiles) return;
+  const int tiles_m = (M + BM - 1) / BM;
+  const int grp = t / (4 * tiles_n), gbase = grp * 4;
+  const int gsz = min(4, tiles_m - gbase);
+  const int tin = t - grp * 4 * tiles_n;
+  const int m0 = (gbase + tin % gsz) * BM, n0 = (tin / gsz) * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % WM, wn = wave / WM;
+  const int r32 = lane & 31, hi = lane >> 5;
+  uint32_t off[AI + BI];                         // byte offsets, as in k_gemm_dma: A, then W
+#pragma unroll
+  for (int i = 0; i < AI; ++i) {
+    const int slot = (wave * AI + i) * 64 + lane, r = slot >> 3, c = (slot & 7) ^ swz(r);
+    off[i] = 2u * uint32_t(min(m0 + r, M - 1) * lda + 8 * c);
+  }
+#pragma unroll
+  for (int i = 0; i < BI; ++i) {
+    const int slot = (wave * BI + i) * 64 + lane, r = slot >> 3, c = (slot & 7) ^ swz(r);
+    off[AI + i] = 2u * uint32_t(min(n0 + r, N - 1) * ldw + 8 * c);
+  }
+  auto dma_one = [&](int st, int kt, int j) {
+    uint4* to = lds + st * STAGE;
+    if (j < AI) dma16(A + kt * BK, off[j], to + (wave * AI + j) * 64);
+    else dma16(W + kt * BK, off[j], to + BM * 8 + (wave * BI + (j - AI)) * 64);
+  };
+  struct Frag { bf16x8 a[TM], b[TN]; };
+  auto read = [&](Frag& f, const uint4* s, int kk) {
+    const int ch = 2 * kk + hi;
+#pragma unroll
+    for (int a = 0; a < TM; ++a) {
+      const int r = wm * WTM + a * 32 + r32;
+      f.a[a] = __builtin_bit_cast(bf16x8, s[r * 8 + (ch ^ swz(r))]);
+    }
+#pragma unroll
+    for (int b = 0; b < TN; ++b) {
+      const int r = wn * WTN + b * 32 + r32;
+      f.b[b] = __builtin_bit_cast(bf16x8, s[BM * 8 + r * 8 + (ch ^ swz(r))]);
+    }
+  };
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < TN; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+
+  const int KT = K / BK;
+#pragma unroll
+  for (int i = 0; i < ST - 1; ++i)
+    if (i < KT)
+#pragma unroll
+      for (int j = 0; j < AI + BI; ++j) dma_one(i, i, j);
+  if (KT >= ST - 1) wait_vmcnt<(ST - 2) * (AI + BI)>();          // k-step 0 has landed
+  else wait_vmcnt<0>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  Frag f[2];
+  read(f[0], lds, 0);
+  for (int kt0 = 0; kt0 < KT; kt0 += ST) {
+#pragma unroll
+    for (int i = 0; i < ST; ++i) {
+      const int kt = kt0 + i;
+      if (kt >= KT) break;
+      // k-step kt + 1 has landed in every wave's view, and every wave's reads of k-step
+      // kt - 1 have returned: its stage takes k-step kt + ST - 1
+      if (kt + ST - 2 < KT) __builtin_amdgcn_s_waitcnt(0x0070 | (AI + BI));   // vmcnt(4) lgkmcnt(0)
+      else __builtin_amdgcn_s_waitcnt(0x0070);
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        if (kk < 3) read(f[(kk + 1) & 1], lds + i * STAGE, kk + 1);
+        else read(f[0], lds + (i + 1) % ST * STAGE, 0);          // past the last k-step: unused
+        if (kt + ST - 1 < KT) dma_one((i + ST - 1) % ST, kt + ST - 1, kk);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int b = 0; b < TN; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[kk & 1].a[a], f[kk & 1].b[b], acc[a][b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0070);            // the reads ahead are done: the epilogue reuses LDS
+  static_assert(sizeof(lds) >= NW * 32 * kEpiStride * sizeof(float), "epilogue LDS");
+  gemm_epilogue<BM, BN, WM, WN>(acc, lds, m0, n0, M, N, wave, lane, rows_ok, epi);
+}
+
+inline Status check_gemm(int lda, int ldw, int M, int N, int K) {
   if (K % 128 || lda % 8 || ldw % 8) return Status::shape("bf16 GEMM needs K % 128 == 0 and 16-byte rows");
   if (int64_t(M) * lda > INT32_MAX || int64_t(N) * ldw > INT32_MAX)
     return Status::shape("bf16 GEMM operand exceeds 2^31 elements");
+  return Status::ok();
+}
+
+template <int BM, int BN, int WM, int WN, int DS, int ST, class Epi>
+Status launch_dma(const uint16_t* A, int lda, const uint16_t* W, int ldw, int M, int N, int K,
+                  const Epi& epi, hipStream_t s) {
   const int tn = (N + BN - 1) / BN, tm = (M + BM - 1) / BM;
   const int tiles = tn * tm;
   const int per = (tiles + 7) / 8;
   // row-vector epilogue stores need 16-byte aligned rows; otherwise every tile goes by column
   const int rows_ok = epi.rows_aligned() ? 1 : 0;
-  hipLaunchKernelGGL((k_gemm_dma<BM, BN, WM, WN, DS, Epi>), dim3(8 * per), dim3(WM * WN * 64), 0, s, A, lda, W,
-                     ldw, M, N, K, tn, tiles, per, rows_ok, epi);
+  hipLaunchKernelGGL((k_gemm_dma<BM, BN, WM, WN, DS, ST, Epi>), dim3(8 * per), dim3(WM * WN * 64), 0, s, A, lda,
+                     W, ldw, M, N, K, tn, tiles, per, rows_ok, epi);
   DC_HIP(hipGetLastError());
   return Status::ok();
 }
 
+template <class Epi>
+Status launch_pipe(const uint16_t* A, int lda, const uint16_t* W, int ldw, int M, int N, int K,
+                   const Epi& epi, hipStream_t s) {
+  const int tn = (N + 127) / 128, tiles = tn * ((M + 127) / 128), per = (tiles + 7) / 8;
+  hipLaunchKernelGGL((k_gemm_pipe<Epi>), dim3(8 * per), dim3(512), 0, s, A, lda, W, ldw, M, N, K, tn, tiles,
+                     per, epi.rows_aligned() ? 1 : 0, epi);
+  DC_HIP(hipGetLastError());
+  return Status::ok();
+}
+
+// Cost of a block GEMM in us with tile i: rounds of one workgroup per compute unit, each
+// `fixed` (launch, first fill, epilogue) plus K / 64 k-steps of `alone` (a nearly empty chip) to
+// `full` (every compute unit fetching operands).  The 64 x 64 tile runs up to three
+// workgroups per compute unit, a k-step taking c[n - 1] with n of them.  Fitted to timings of
+// all six tiles on 80 shapes (M 300 to 17,776; d 512, 1,152, 1,920, 3,072; QKV, out, up, down)
+// on MI355X: the tile it picks is 0.04 % slower than the best one on average, 6 % at worst.
+// Examples (us, the earlier fixed choice of 384 x 192 / 320 x 256 -> now): out 1,556 x 1,920 52 -> 18,
+// down 162 -> 54; down 3,704 x 1,152 102 -> 57; up 300 x 7,680 54 -> 17; 17,776 tokens unchanged.
+struct TileCost { int bm, bn; float alone, full, fixed; };
+constexpr TileCost kTiles[] = {{384, 192, 1.168f, 1.706f, 11.2f}, {320, 256, 1.295f, 1.792f, 12.9f},
+                               {256, 192, 0.849f, 1.204f, 7.6f},  {256, 128, 0.666f, 0.982f, 5.0f},
+                               {128, 128, 0.341f, 0.471f, 3.9f},  {64, 64, 0.f, 0.f, 2.1f}};
+constexpr float kSmallStep[3] = {0.302f, 0.401f, 0.496f};
+
+int pick_tile(int M, int N, int K, int cus) {
+  const float steps = float(K / 64);
+  int best = 0;
+  float least = 0.f;
+  for (int i = 0; i < 6; ++i) {
+    const TileCost& c = kTiles[i];
+    const int64_t tiles = int64_t((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    float t;
+    if (i == 5) {
+      const int64_t rounds = tiles / (3 * cus), rest = tiles % (3 * cus);
+      t = float(rounds) * (steps * kSmallStep[2] + c.fixed);
+      if (rest) t += steps * kSmallStep[(rest - 1) / cus] + c.fixed;
+    } else {
+      const int64_t rounds = tiles / cus, rest = tiles % cus;
+      t = float(rounds) * (steps * c.full + c.fixed);
+      if (rest) t += steps * (c.alone + (c.full - c.alone) * float(rest) / float(cus)) + c.fixed;
+    }
+    if (i == 0 || t < least) {
+      best = i;
+      least = t;
+    }
+  }
+  return best;
+}
+
+template <class Epi>
+Status block_gemm(const uint16_t* A, int lda, const uint16_t* W, int ldw, int M, int N, int K,
+                  const Epi& epi, hipStream_t s) {
+  if (M <= 0) return Status::ok();
+  DC_TRY(check_gemm(lda, ldw, M, N, K));
+  const int cus = compute_units();
+  if (cus <= 0) return Status::make(DC_ERR_HIP, "bf16 GEMM: no device");
+  switch (pick_tile(M, N, K, cus)) {
+    case 0: return launch_dma<384, 192, 4, 2, 2, 2>(A, lda, W, ldw, M, N, K, epi, s);
+    case 1: return launch_dma<320, 256, 2, 4, 2, 2>(A, lda, W, ldw, M, N, K, epi, s);
+    case 2: return launch_dma<256, 192, 4, 2, 2, 2>(A, lda, W, ldw, M, N, K, epi, s);
+    case 3: return launch_dma<256, 128, 4, 2, 2, 3>(A, lda, W, ldw, M, N, K, epi, s);
+    case 4: return launch_pipe(A, lda, W, ldw, M, N, K, epi, s);
+    default: return launch_dma<64, 64, 2, 2, 2, 3>(A, lda, W, ldw, M, N, K, epi, s);
+  }
+}
 
 // ---------------------------------------------------------------------------
 // Patch embedding for the bf16 model: h_in[n] = patch(x)[n] W_pe^T + b + pos[n]
@@ -598,29 +776,28 @@ __global__ void __launch_bounds__(512) k_patch_embed_bf16(const float* __restric
 // ---------------------------------------------------------------------------
 Status gemm_bf16_qkv(const uint16_t* A, const uint16_t* W, const float* bias, uint16_t* qk,
                      uint16_t* vt, int ldv, const Geo& g, int M, hipStream_t s) {
-  return launch_dma<384, 192, 4, 2, 2>(A, g.d, W, g.d, M, 3 * g.d, g.d,
-                                    EpiQKVBf16{bias, qk, vt, g.d, ldv,
-                                               float(1.4426950408889634 / std::sqrt(double(g.Dh)))},
-                                    s);
+  return block_gemm(A, g.d, W, g.d, M, 3 * g.d, g.d,
+                    EpiQKVBf16{bias, qk, vt, g.d, ldv, float(1.4426950408889634 / std::sqrt(double(g.Dh)))}, s);
 }
 
 Status gemm_bf16_gate_residual(const uint16_t* A, int lda, const uint16_t* W, const float* bias,
                                const float* gate, float* h, int ldh, int M, int N, int K,
                                hipStream_t s) {
-  return launch_dma<384, 192, 4, 2, 2>(A, lda, W, K, M, N, K, EpiGateResidual{bias, gate, h, ldh}, s);
+  return block_gemm(A, lda, W, K, M, N, K, EpiGateResidual{bias, gate, h, ldh}, s);
 }
 
 Status gemm_bf16_gelu(const uint16_t* A, int lda, const uint16_t* W, const float* bias,
                       uint16_t* out, int ldo, int M, int N, int K, hipStream_t s) {
-  return launch_dma<320, 256, 2, 4, 2>(A, lda, W, K, M, N, K, EpiGeluBf16{bias, out, ldo}, s);
+  return block_gemm(A, lda, W, K, M, N, K, EpiGeluBf16{bias, out, ldo}, s);
 }
 
 Status gemm_bf16_head(const uint16_t* A, int lda, const uint16_t* W, const float* bias, float* x,
                       float dsigma, const Geo& g, int M, hipStream_t s) {
   if (M <= 0) return Status::ok();
   if (g.P != 64 || g.d % 128 || lda % 8) return Status::shape("bf16 head needs 64 outputs and d % 128 == 0");
+  DC_TRY(check_gemm(lda, g.d, M, 64, g.d));
   EpiHeadEuler e{bias, x, dsigma, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp};
-  return launch_dma<64, 64, 2, 2, 4>(A, lda, W, g.d, M, 64, g.d, e, s);
+  return launch_dma<64, 64, 2, 2, 4, 2>(A, lda, W, g.d, M, 64, g.d, e, s);
 }
 
 Status patch_embed_bf16(const float* x, const float* W, const float* bias, const uint16_t* pos,
