@@ -78,7 +78,6 @@ Status make_idx(const int32_t* idx, int32_t n, IdxList& out) {
 Workspace workspace_layout(const Geo& g, int batch) {
   Workspace w{};
   w.ldv = (g.N + 63) / 64 * 64;
-  w.kTmax = 64;
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
   w.a = take(size_t(g.N) * g.d * g.esz);
@@ -95,11 +94,11 @@ Workspace workspace_layout(const Geo& g, int batch) {
   // 128 queries x (head_dim + 4) floats each
   w.attn_part_bytes = g.bf16 ? size_t(8) * 64 * 2 * 128 * (g.Dh + 4) * sizeof(float) : 0;
   w.attn_part = take(w.attn_part_bytes);
-  w.tm_e = take(size_t(w.kTmax) * 256 * 4);
-  w.tm_h = take(size_t(w.kTmax) * g.d * 4);
-  w.tm_c = take(size_t(w.kTmax) * g.d * 4);
-  w.tm_s = take(size_t(w.kTmax) * g.d * 4);
-  w.tm_m = take(size_t(w.kTmax) * 6 * g.d * 4 + size_t(w.kTmax) * sizeof(double));
+  w.tm_e = take(size_t(kModSteps) * 256 * 4);
+  w.tm_h = take(size_t(kModSteps) * g.d * 4);
+  w.tm_c = take(size_t(kModSteps) * g.d * 4);
+  w.tm_s = take(size_t(kModSteps) * g.d * 4);
+  w.tm_m = take(size_t(kModSteps) * 6 * g.d * 4);
   w.total = off;
   return w;
 }
@@ -130,25 +129,24 @@ Status time_modulation(const Geo& g, const dc_model_weights* w, const double* si
   if (!w->blocks) return Status::arg("weights->blocks is NULL");
   Workspace L;
   DC_TRY(check_ws(g, 1, ws, ws_bytes, L));
-  double* sig = at<double>(ws, L.tm_m + size_t(L.kTmax) * 6 * g.d * 4);
-  for (int k0 = 0; k0 < K; k0 += L.kTmax) {
-    const int kc = std::min(L.kTmax, K - k0);
-    DC_HIP(hipMemcpyAsync(sig, sigmas + k0, sizeof(double) * kc, hipMemcpyHostToDevice, s));
-    float* e = at<float>(ws, L.tm_e);
-    float* hdn = at<float>(ws, L.tm_h);
-    float* c = at<float>(ws, L.tm_c);
-    float* sc = at<float>(ws, L.tm_s);
-    float* m = at<float>(ws, L.tm_m);
-    DC_TRY(time_features(sig, kc, e, 256, s));
+  std::vector<const float*> offsets(size_t(g.L));
+  for (int l = 0; l < g.L; ++l) {
+    offsets[size_t(l)] = w->blocks[l].mod_offset;
+    if (!offsets[size_t(l)]) return Status::arg("mod_offset is NULL");
+  }
+  float* e = at<float>(ws, L.tm_e);
+  float* hdn = at<float>(ws, L.tm_h);
+  float* c = at<float>(ws, L.tm_c);
+  float* sc = at<float>(ws, L.tm_s);
+  float* m = at<float>(ws, L.tm_m);
+  for (int k0 = 0; k0 < K; k0 += kModSteps) {
+    const int kc = std::min(kModSteps, K - k0);
+    DC_TRY(time_features(sigmas + k0, kc, e, 256, s));
     DC_TRY(gemm_f32_bias_act(e, 256, w->w_t1, 256, w->b_t1, hdn, g.d, kc, g.d, 256, Act::kSilu, s));
-    DC_TRY(gemm_f32_bias_act(hdn, g.d, w->w_t2, g.d, w->b_t2, c, g.d, kc, g.d, g.d, Act::kNone, s));
-    DC_TRY(silu_inplace(c, sc, size_t(kc) * g.d, s));
+    DC_TRY(gemm_f32_bias_and_silu(hdn, g.d, w->w_t2, g.d, w->b_t2, c, sc, g.d, kc, g.d, g.d, s));
     DC_TRY(gemm_f32_bias_act(sc, g.d, w->w_m, g.d, w->b_m, m, 6 * g.d, kc, 6 * g.d, g.d, Act::kNone, s));
-    for (int l = 0; l < g.L; ++l) {
-      if (!w->blocks[l].mod_offset) return Status::arg("mod_offset is NULL");
-      DC_TRY(assemble_modulation(m, c, w->blocks[l].mod_offset, kc, g.L, l, g, mod, k0, s));
-    }
-    DC_TRY(assemble_modulation(m, c, w->head_mod, kc, g.L, g.L, g, mod, k0, s));
+    DC_TRY(assemble_modulation(m, c, offsets.data(), w->head_mod, kc, g,
+                               mod + size_t(k0) * (g.L + 1) * 6 * g.d, s));
   }
   return Status::ok();
 }

@@ -2,9 +2,10 @@
 // v_mfma_f32_16x16x4_f32 (fp32 operands, fp32 accumulation).
 //
 // softmax(Q K^T / sqrt(d_h)) V per head over qkv [M, 3d] (Q | K | V, head-major columns),
-// head_dim 64, with an online softmax.  The tangent form also takes dqkv [M, 3d] and
-// returns, with ds = (dq.k + q.dk) / sqrt(d_h) and P the softmax,
-//   do = sum_j P_j (ds_j - sum_i P_i ds_i) v_j + P_j dv_j.
+// head_dim 64, with an online softmax.  The tangent form takes n tangents dqkv stacked below
+// qkv and returns for each, with ds = (dq.k + q.dk) / sqrt(d_h) and P the softmax,
+//   do = sum_j P_j (ds_j - sum_i P_i ds_i) v_j + P_j dv_j
+// stacked below o.
 //
 // These calls are short (272 tokens x 4 heads in the small model), so what bounds them is
 // the length of the serial chain over the keys and how few wavefronts there are: a
@@ -52,11 +53,9 @@ __device__ inline float over_groups_sum(float v) {
 
 // c2 = log2(e) / sqrt(d_h): exponentials are 2^(c2 (s - m)); rs = 1 / sqrt(d_h).
 template <int QB, int KS, bool kTan>
-__global__ void __launch_bounds__(KS * 64) k_attn_f32(const float* __restrict__ qkv,
-                                                      const float* __restrict__ dqkv, int M, int d,
+__global__ void __launch_bounds__(KS * 64) k_attn_f32(const float* __restrict__ qkv, int M, int d,
                                                       float c2, float rs, int nqb, int items,
-                                                      int per_xcd, float* __restrict__ out,
-                                                      float* __restrict__ dout) {
+                                                      int per_xcd, float* __restrict__ out) {
   constexpr int NT = kTan ? 2 : 1;                  // accumulated tensors: O (and the tangent's sums)
   __shared__ float s_m[KS][QB * 16], s_l[KS][QB * 16], s_c[KS][QB * 16];
   __shared__ __attribute__((aligned(16))) float s_o[NT][KS][QB * 16 * kOs];
@@ -71,7 +70,8 @@ __global__ void __launch_bounds__(KS * 64) k_attn_f32(const float* __restrict__ 
   const float* Qb = qkv + head * kDh;
   const float* Kb = Qb + d;
   const float* Vb = Qb + 2 * d;
-  const ptrdiff_t tan = kTan ? dqkv - qkv : 0;      // from a primal element to its tangent
+  // tangent blockIdx.y: from a primal element to its tangent
+  const size_t tan = kTan ? size_t(blockIdx.y + 1) * M * ld : 0;
 
   f32x4 qf[QB][4], dqf[kTan ? QB : 1][4];
 #pragma unroll
@@ -237,18 +237,18 @@ __global__ void __launch_bounds__(KS * 64) k_attn_f32(const float* __restrict__ 
     }
     const float inv = 1.0f / lt;
     const size_t dst = size_t(q0 + q) * d + head * kDh + c4;
-    *reinterpret_cast<f32x4*>(out + dst) = a * inv;
-    if constexpr (kTan) *reinterpret_cast<f32x4*>(dout + dst) = (t - a * (ct * inv)) * inv;
+    if (!kTan || blockIdx.y == 0) *reinterpret_cast<f32x4*>(out + dst) = a * inv;
+    if constexpr (kTan)
+      *reinterpret_cast<f32x4*>(out + size_t(blockIdx.y + 1) * M * d + dst) = (t - a * (ct * inv)) * inv;
   }
 }
 
 template <int QB, int KS, bool kTan>
-Status launch(const float* qkv, const float* dqkv, const Geo& g, int M, float* o, float* dout,
-              hipStream_t s) {
+Status launch(const float* qkv, int n, const Geo& g, int M, float* o, hipStream_t s) {
   const int nqb = (M + 16 * QB - 1) / (16 * QB), items = nqb * g.H, per_xcd = (items + 7) / 8;
   const double rs = 1.0 / std::sqrt(double(g.Dh));
-  hipLaunchKernelGGL((k_attn_f32<QB, KS, kTan>), dim3(8 * per_xcd), dim3(KS * 64), 0, s, qkv, dqkv, M,
-                     g.d, float(1.4426950408889634 * rs), float(rs), nqb, items, per_xcd, o, dout);
+  hipLaunchKernelGGL((k_attn_f32<QB, KS, kTan>), dim3(8 * per_xcd, n), dim3(KS * 64), 0, s, qkv, M, g.d,
+                     float(1.4426950408889634 * rs), float(rs), nqb, items, per_xcd, o);
   DC_HIP(hipGetLastError());
   return Status::ok();
 }
@@ -270,16 +270,15 @@ Status attention_f32(const float* qkv, float* out, const Geo& g, int M, hipStrea
   if (cus <= 0) return Status::make(DC_ERR_HIP, "fp32 attention: no device");
   const int64_t r16 = (int64_t(g.H) * ((M + 15) / 16) + cus - 1) / cus;
   const int64_t r32 = (int64_t(g.H) * ((M + 31) / 32) + cus - 1) / cus;
-  if (9 * r32 < 5 * r16) return launch<2, 4, false>(qkv, nullptr, g, M, out, nullptr, s);
-  if (r16 > 1) return launch<1, 4, false>(qkv, nullptr, g, M, out, nullptr, s);
-  return launch<1, 8, false>(qkv, nullptr, g, M, out, nullptr, s);
+  if (9 * r32 < 5 * r16) return launch<2, 4, false>(qkv, 1, g, M, out, s);
+  if (r16 > 1) return launch<1, 4, false>(qkv, 1, g, M, out, s);
+  return launch<1, 8, false>(qkv, 1, g, M, out, s);
 }
 
-Status attention_jvp_f32(const float* qkv, const float* dqkv, const Geo& g, int M, float* o,
-                         float* dout, hipStream_t s) {
+Status attention_jvp_f32(const float* qkv, int n, const Geo& g, int M, float* o, hipStream_t s) {
   if (g.Dh != kDh) return Status::shape("calibration attention tangent supports head_dim 64");
-  if (M <= 0) return Status::ok();
-  return launch<1, 4, true>(qkv, dqkv, g, M, o, dout, s);
+  if (M <= 0 || n <= 0) return Status::ok();
+  return launch<1, 4, true>(qkv, n, g, M, o, s);
 }
 
 }  // namespace dc

@@ -12,6 +12,12 @@
 //          t moves by e: dx = (sigma_{t+1} - sigma_t) e, then for every later step k
 //          dx += (sigma_{k+1} - sigma_k) J_k dx, J_k the Jacobian of the full network at
 //          x_k (a Jacobian-vector product: the network run in tangent mode).
+// J_k does not depend on the perturbation, so the runs are taken in groups of up to T tangents
+// (ordered by t = j + h) that go through the steps together: one network pass per step
+// carries the primal activations and every active tangent of the group, stacked as rows of the
+// same GEMMs.  T fills about 4,096 rows; one tangent at a time (the small fp32 model: 64 passes
+// of the network with its tangent, 2,900 launches, a wait per norm) took 15.5 ms, the groups
+// take 3.4 ms.  The norms are read back once, at the end.
 // Runs with j + h > K price nothing and stay 0.  The trace runs the library's own
 // kernels for the model's dtype (bf16 models: bf16 MFMA blocks); r, u, the perturbations
 // and every tangent are fp32 (calib.hip and the fp32 GEMMs, with bf16 weights widened
@@ -38,9 +44,14 @@ namespace {
 inline size_t al256(size_t v) { return (v + 255) & ~size_t(255); }
 
 struct CalibLayout {
-  size_t blk, blk_bytes, mod, xs, us, rs, h_in, h, dh, a, da, qkv, dqkv, o, dout, z, dz, patches,
-      zeros, v1, v2, e, G, dx, red, red_out, total;
+  size_t blk, blk_bytes, mod, xs, us, rs, h_in, h, a, qkv, o, z, patches, zeros, v, dx, G, red, norms, total;
+  int T;                 // tangents per group
 };
+
+// one (j, h) entry: a run refreshed at j, perturbed at step t = j + h
+struct Run { int j, h, t; };
+
+inline int max_runs(int K) { return K * (K - 1) / 2; }    // j + h <= K, any h_max
 
 CalibLayout calib_layout(const Geo& g, int K) {
   CalibLayout c{};
@@ -48,6 +59,8 @@ CalibLayout calib_layout(const Geo& g, int K) {
   auto take = [&](size_t bytes) { const size_t o = off; off = al256(off + bytes); return o; };
   const size_t N = size_t(g.N), Nv = size_t(g.Nv), d = size_t(g.d), F = size_t(g.F);
   const size_t lat = size_t(g.C) * g.T * g.Hl * g.Wl;
+  c.T = std::max(1, std::min(kMaxTangents, 4096 / g.N));
+  const size_t R = size_t(c.T + 1) * N;            // rows of a stack: the primal and T tangents
   c.blk_bytes = workspace_layout(g, 1).total;
   c.blk = take(c.blk_bytes);
   c.mod = take(size_t(K) * (g.L + 1) * 6 * d * 4);
@@ -55,25 +68,18 @@ CalibLayout calib_layout(const Geo& g, int K) {
   c.us = take(size_t(K) * Nv * d * 4);
   c.rs = take(size_t(K) * Nv * d * 4);
   c.h_in = take(N * d * 4);
-  c.h = take(N * d * 4);
-  c.dh = take(N * d * 4);
-  c.a = take(N * d * 4);
-  c.da = take(N * d * 4);
-  c.qkv = take(N * 3 * d * 4);
-  c.dqkv = take(N * 3 * d * 4);
-  c.o = take(N * d * 4);
-  c.dout = take(N * d * 4);
-  c.z = take(N * F * 4);
-  c.dz = take(N * F * 4);
-  c.patches = take(Nv * 64 * 4);
-  c.zeros = take(std::max(std::max(3 * d, F), size_t(64)) * 4);
-  c.v1 = take(lat * 4);
-  c.v2 = take(lat * 4);
-  c.e = take(lat * 4);
-  c.G = take(lat * 4);
-  c.dx = take(lat * 4);
+  c.h = take(R * d * 4);
+  c.a = take(R * d * 4);
+  c.qkv = take(R * 3 * d * 4);
+  c.o = take(R * d * 4);
+  c.z = take(R * F * 4);
+  c.patches = take(size_t(c.T) * N * 64 * 4);
+  c.zeros = take(d * 4);
+  c.v = take(size_t(c.T + 1) * lat * 4);
+  c.dx = take(size_t(c.T) * lat * 4);
+  c.G = take(size_t(K) * lat * 4);
   c.red = take(sumsq_scratch_doubles() * 8);
-  c.red_out = take(2 * 8);
+  c.norms = take((2 * size_t(max_runs(K)) + 1) * 2 * 8);
   c.total = off;
   return c;
 }
@@ -100,15 +106,9 @@ struct Calib {
   float* x_at(int k) const { return F(L.xs) + size_t(k - 1) * lat; }        // x_k, k = 1..K+1
   float* u_at(int k) const { return F(L.us) + size_t(k - 1) * g.Nv * g.d; }
   float* r_at(int k) const { return F(L.rs) + size_t(k - 1) * g.Nv * g.d; }
+  float* G_at(int j) const { return F(L.G) + size_t(j - 1) * lat; }         // sum of P e over the run
+  float* dx_at(int i) const { return F(L.dx) + size_t(i) * lat; }           // tangent i of the group
   float dsig(int k) const { return float(sig[k] - sig[k - 1]); }            // step k: sigma_{k+1} - sigma_k
-
-  // (sum (a - b)^2, sum a^2) over n elements, read back (one wait)
-  Status norms(const float* a, const float* b, size_t n, double out[2]) {
-    DC_TRY(sumsq(a, b, n, at<double>(ws, L.red), at<double>(ws, L.red_out), s));
-    DC_HIP(hipMemcpyAsync(out, at<double>(ws, L.red_out), 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-    DC_HIP(hipStreamSynchronize(s));
-    return Status::ok();
-  }
 
   // full trace: x_1..x_{K+1}, u_k, r_k
   Status trace(const float* x1) {
@@ -128,74 +128,56 @@ struct Calib {
     return Status::ok();
   }
 
-  // v = H_k(x_k, r) into out: the head of g = h_in(x_k)[video] + r, as x = 0 + 1 v
-  Status interface(int k, const float* r, float* out) {
-    const float* mk = mod_k(k);
-    DC_TRY(patch_embed(g, w, x_at(k), txt, F(L.h_in), one, blk(), L.blk_bytes, s));
-    DC_TRY(lincomb(F(L.h), F(L.h_in), 1.0f, r, 1.0f, size_t(g.Nv) * g.d, s));         // g = h_in + r
-    DC_HIP(hipMemsetAsync(out, 0, lat * 4, s));
-    return head_euler(g, w, mk + size_t(g.L) * 6 * g.d, F(L.h), out, 1.0f, one, blk(), L.blk_bytes, s,
-                      nullptr);
-  }
-
-  // the fp32 GEMMs with the model's weights (fp32, or bf16 widened on load)
-  Status mm(const float* A, int lda, const void* W, int ldw, const float* bias, float* out, int ldo,
-            int M, int N, int Kd) const {
-    if (g.bf16)
-      return gemm_f32_bias_act(A, lda, static_cast<const uint16_t*>(W), ldw, bias, out, ldo, M, N, Kd,
-                               Act::kNone, s);
-    return gemm_f32_bias_act(A, lda, static_cast<const float*>(W), ldw, bias, out, ldo, M, N, Kd,
-                             Act::kNone, s);
-  }
-  Status mm_gate(const float* A, int lda, const void* W, int ldw, const float* bias, const float* gate,
-                 float* h, int M, int N, int Kd) const {
-    if (g.bf16)
-      return gemm_f32_gate_residual(A, lda, static_cast<const uint16_t*>(W), ldw, bias, gate, h, g.d, M,
-                                    N, Kd, s);
-    return gemm_f32_gate_residual(A, lda, static_cast<const float*>(W), ldw, bias, gate, h, g.d, M, N,
-                                  Kd, s);
-  }
-
-  // one block in tangent mode on (h, dh)
-  Status block_jvp(int l, const float* m6) {
-    const dc_block_weights& b = w->blocks[l];
-    const int N = g.N, d = g.d, Fh = g.F;
-    const float* zeros = F(L.zeros);
-    const float *sh1 = m6, *sc1 = m6 + d, *g1 = m6 + 2 * d, *sh2 = m6 + 3 * d, *sc2 = m6 + 4 * d,
-                *g2 = m6 + 5 * d;
-    DC_TRY(ln_mod_jvp(F(L.h), F(L.dh), N, d, d, sh1, sc1, F(L.a), F(L.da), g.eps, s));
-    DC_TRY(mm(F(L.a), d, b.w_qkv, d, b.b_qkv, F(L.qkv), 3 * d, N, 3 * d, d));
-    DC_TRY(mm(F(L.da), d, b.w_qkv, d, zeros, F(L.dqkv), 3 * d, N, 3 * d, d));
-    DC_TRY(attention_jvp_f32(F(L.qkv), F(L.dqkv), g, N, F(L.o), F(L.dout), s));
-    DC_TRY(mm_gate(F(L.o), d, b.w_o, d, b.b_o, g1, F(L.h), N, d, d));
-    DC_TRY(mm_gate(F(L.dout), d, b.w_o, d, zeros, g1, F(L.dh), N, d, d));
-    DC_TRY(ln_mod_jvp(F(L.h), F(L.dh), N, d, d, sh2, sc2, F(L.a), F(L.da), g.eps, s));
-    DC_TRY(mm(F(L.a), d, b.w_1, d, b.b_1, F(L.z), Fh, N, Fh, d));
-    DC_TRY(mm(F(L.da), d, b.w_1, d, zeros, F(L.dz), Fh, N, Fh, d));
-    DC_TRY(gelu_jvp(F(L.z), F(L.dz), size_t(N) * Fh, s));
-    DC_TRY(mm_gate(F(L.z), Fh, b.w_2, Fh, b.b_2, g2, F(L.h), N, d, Fh));
-    DC_TRY(mm_gate(F(L.dz), Fh, b.w_2, Fh, zeros, g2, F(L.dh), N, d, Fh));
+  // dx of runs [i0, i1) of the group, all perturbed at step t: the Euler step of Eq. 6's e.
+  // H_t(x_t, r) is the head of g = h_in(x_t)[video] + r, as x = 0 + 1 v.
+  Status perturb(const Run* runs, int i0, int i1, int t) {
+    const float* mt = mod_k(t);
+    const int n = i1 - i0;
+    const float* r[kMaxTangents + 1];
+    for (int i = 0; i < n; ++i) r[i] = r_at(runs[i0 + i].j);
+    r[n] = r_at(t);
+    DC_TRY(patch_embed(g, w, x_at(t), txt, F(L.h_in), one, blk(), L.blk_bytes, s));
+    DC_TRY(add_each(F(L.h_in), r, n + 1, size_t(g.Nv) * g.d, F(L.h), size_t(g.N) * g.d, s));
+    DC_HIP(hipMemsetAsync(F(L.v), 0, size_t(n + 1) * lat * 4, s));
+    int32_t ids[kMaxTangents + 1];
+    for (int i = 0; i <= n; ++i) ids[i] = i;
+    IdxList il;
+    DC_TRY(make_idx(ids, n + 1, il));
+    DC_TRY(head_euler(g, w, mt + size_t(g.L) * 6 * g.d, F(L.h), F(L.v), 1.0f, il, blk(), L.blk_bytes, s, nullptr));
+    for (int i = 0; i < n; ++i)
+      DC_TRY(scaled_diff(dx_at(i0 + i), F(L.v) + size_t(i) * lat, F(L.v) + size_t(n) * lat, dsig(t), lat, s));
     return Status::ok();
   }
 
-  // dx += (sigma_{k+1} - sigma_k) J_k dx: the whole network at x_k in tangent mode
-  Status step_jvp(int k, float* dx) {
+  // one block on the stack h of the primal and n tangents
+  Status block_jvp(int l, const float* m6, int n) {
+    const dc_block_weights& b = w->blocks[l];
+    const int N = g.N, d = g.d, Fh = g.F, R = (n + 1) * N;
+    const float *sh1 = m6, *sc1 = m6 + d, *g1 = m6 + 2 * d, *sh2 = m6 + 3 * d, *sc2 = m6 + 4 * d,
+                *g2 = m6 + 5 * d;
+    DC_TRY(ln_mod_jvp(F(L.h), n, N, d, sh1, sc1, F(L.a), g.eps, s));
+    DC_TRY(gemm_f32_rows(F(L.a), d, b.w_qkv, g.bf16, d, b.b_qkv, N, F(L.qkv), 3 * d, R, 3 * d, d, s));
+    DC_TRY(attention_jvp_f32(F(L.qkv), n, g, N, F(L.o), s));
+    DC_TRY(gemm_f32_gate_residual_rows(F(L.o), d, b.w_o, g.bf16, d, b.b_o, N, g1, F(L.h), d, R, d, d, s));
+    DC_TRY(ln_mod_jvp(F(L.h), n, N, d, sh2, sc2, F(L.a), g.eps, s));
+    DC_TRY(gemm_f32_rows(F(L.a), d, b.w_1, g.bf16, d, b.b_1, N, F(L.z), Fh, R, Fh, d, s));
+    DC_TRY(gelu_jvp(F(L.z), n, size_t(N) * Fh, s));
+    return gemm_f32_gate_residual_rows(F(L.z), Fh, b.w_2, g.bf16, Fh, b.b_2, N, g2, F(L.h), d, R, d, Fh, s);
+  }
+
+  // dx += (sigma_{k+1} - sigma_k) J_k dx for the first n tangents of the group: the whole
+  // network at x_k, primal and tangents
+  Status step_jvp(int k, int n) {
     const float* mk = mod_k(k);
-    const int d = g.d;
+    const int d = g.d, N = g.N;
     DC_TRY(patch_embed(g, w, x_at(k), txt, F(L.h), one, blk(), L.blk_bytes, s));
-    DC_TRY(patchify(dx, F(L.patches), g, s));              // text rows carry no tangent
-    DC_TRY(gemm_f32_bias_act(F(L.patches), 64, w->w_pe, 64, F(L.zeros), F(L.dh), d, g.Nv, d, 64,
-                             Act::kNone, s));
-    if (g.Nt > 0)
-      DC_HIP(hipMemsetAsync(F(L.dh) + size_t(g.Nv) * d, 0, size_t(g.Nt) * d * 4, s));
-    for (int l = 0; l < g.L; ++l) DC_TRY(block_jvp(l, mk + size_t(l) * 6 * d));
+    DC_TRY(patchify_tangents(F(L.dx), F(L.patches), g, n, s));            // text rows carry no tangent
+    DC_TRY(gemm_f32_rows(F(L.patches), 64, w->w_pe, false, 64, F(L.zeros), 0, F(L.h) + size_t(N) * d, d, n * N, d,
+                         64, s));
+    for (int l = 0; l < g.L; ++l) DC_TRY(block_jvp(l, mk + size_t(l) * 6 * d, n));
     const float* hm = mk + size_t(g.L) * 6 * d;
-    DC_TRY(ln_mod_jvp(F(L.h), F(L.dh), g.Nv, d, d, hm, hm + d, F(L.a), F(L.da), g.eps, s));
-    if (g.bf16)
-      return gemm_f32_head(F(L.da), d, static_cast<const uint16_t*>(w->w_head), F(L.zeros), dx, dsig(k), g,
-                           g.Nv, s);
-    return gemm_f32_head(F(L.da), d, static_cast<const float*>(w->w_head), F(L.zeros), dx, dsig(k), g,
-                         g.Nv, s);
+    DC_TRY(ln_mod_jvp(F(L.h), n, N, d, hm, hm + d, F(L.a), g.eps, s));
+    return gemm_f32_head_tangents(F(L.a) + size_t(N) * d, w->w_head, g.bf16, F(L.dx), dsig(k), g, n, s);
   }
 };
 
@@ -221,35 +203,61 @@ Status calibrate_tables(const Geo& g, const dc_model_weights* w, const float* x1
   Calib c{g, w, txt, sigmas, K, ws, L, s, {}, size_t(g.C) * g.T * g.Hl * g.Wl, size_t(g.L + 1) * 6 * g.d};
   const int32_t zero = 0;
   DC_TRY(make_idx(&zero, 1, c.one));
-  DC_HIP(hipMemsetAsync(c.F(L.zeros), 0, std::max(std::max(3 * size_t(g.d), size_t(g.F)), size_t(64)) * 4, s));
+  DC_HIP(hipMemsetAsync(c.F(L.zeros), 0, size_t(g.d) * 4, s));
+  DC_HIP(hipMemsetAsync(c.F(L.G), 0, size_t(K) * c.lat * 4, s));
   DC_TRY(time_modulation(g, w, sigmas, K, c.F(L.mod), c.blk(), L.blk_bytes, s));
   DC_TRY(c.trace(x1));
+
+  // every run, ordered by the step it is perturbed at (and by h, so the sums of Eq. 7 grow in order)
+  std::vector<Run> runs;
+  for (int t = 2; t <= K; ++t)
+    for (int h = 1; h <= h_max && h < t; ++h) runs.push_back({t - h, h, t});
+  const int n_runs = int(runs.size());
+
+  // norms: n_runs of Eq. 5, then n_runs of Eq. 7, then the terminal latent's
+  double* norms = at<double>(ws, L.norms);
+  {
+    std::vector<const float*> a, b;
+    for (const Run& r : runs) {
+      a.push_back(c.u_at(r.t));
+      b.push_back(c.u_at(r.j));
+    }
+    DC_TRY(sumsq(a.data(), b.data(), n_runs, size_t(g.Nv) * g.d, at<double>(ws, L.red), norms, s));
+    const float* out = c.x_at(K + 1);
+    DC_TRY(sumsq(&out, nullptr, 1, c.lat, at<double>(ws, L.red), norms + 4 * size_t(n_runs), s));
+  }
+  for (int g0 = 0; g0 < n_runs; g0 += L.T) {
+    const Run* grp = runs.data() + g0;
+    const int n = std::min(L.T, n_runs - g0);
+    for (int i = 0; i < n;) {
+      int e = i + 1;
+      while (e < n && grp[e].t == grp[i].t) ++e;
+      DC_TRY(c.perturb(grp, i, e, grp[i].t));
+      i = e;
+    }
+    for (int k = grp[0].t + 1, active = 0; k <= K; ++k) {
+      while (active < n && grp[active].t < k) ++active;
+      DC_TRY(c.step_jvp(k, active));
+    }
+    for (int i = 0; i < n; ++i) {
+      float* G = c.G_at(grp[i].j);                        // G_{j,h} = G_{j,h-1} + P_{j+h} e
+      DC_TRY(lincomb(G, G, 1.0f, c.dx_at(i), 1.0f, c.lat, s));
+      const float* Gc = G;
+      DC_TRY(sumsq(&Gc, nullptr, 1, c.lat, at<double>(ws, L.red), norms + 2 * size_t(n_runs + g0 + i), s));
+    }
+  }
+  std::vector<double> host(2 * (2 * size_t(n_runs) + 1));
+  DC_HIP(hipMemcpyAsync(host.data(), norms, host.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+  DC_HIP(hipStreamSynchronize(s));
 
   const size_t T = size_t(K - 1) * h_max;
   std::fill(q, q + T, 0.0);
   std::fill(dtab, dtab + T, 0.0);
-  double nx[2];
-  DC_TRY(c.norms(c.x_at(K + 1), nullptr, c.lat, nx));
-  const double xn = std::sqrt(nx[1]);
-  const size_t nu = size_t(g.Nv) * g.d;
-  for (int j = 1; j < K; ++j) {
-    DC_HIP(hipMemsetAsync(c.F(L.G), 0, c.lat * 4, s));
-    for (int h = 1; h <= h_max && j + h <= K; ++h) {
-      const int t = j + h;
-      double du[2];
-      DC_TRY(c.norms(c.u_at(t), c.u_at(j), nu, du));
-      dtab[size_t(j - 1) * h_max + (h - 1)] = std::sqrt(du[0]) / (std::sqrt(du[1]) + eps);
-      // Eq. 6, then the tail of Eq. 7
-      DC_TRY(c.interface(t, c.r_at(j), c.F(L.v1)));
-      DC_TRY(c.interface(t, c.r_at(t), c.F(L.v2)));
-      DC_TRY(lincomb(c.F(L.e), c.F(L.v1), 1.0f, c.F(L.v2), -1.0f, c.lat, s));       // e = v1 - v2
-      DC_TRY(lincomb(c.F(L.dx), c.F(L.e), c.dsig(t), nullptr, 0.0f, c.lat, s));     // its Euler step
-      for (int k = t + 1; k <= K; ++k) DC_TRY(c.step_jvp(k, c.F(L.dx)));
-      DC_TRY(lincomb(c.F(L.G), c.F(L.G), 1.0f, c.F(L.dx), 1.0f, c.lat, s));
-      double gn[2];
-      DC_TRY(c.norms(c.F(L.G), nullptr, c.lat, gn));
-      q[size_t(j - 1) * h_max + (h - 1)] = std::sqrt(gn[1]) / (xn + eps);
-    }
+  const double xn = std::sqrt(host[4 * size_t(n_runs) + 1]);
+  for (int i = 0; i < n_runs; ++i) {
+    const size_t e = size_t(runs[size_t(i)].j - 1) * h_max + (runs[size_t(i)].h - 1);
+    dtab[e] = std::sqrt(host[2 * size_t(i)]) / (std::sqrt(host[2 * size_t(i) + 1]) + eps);
+    q[e] = std::sqrt(host[2 * size_t(n_runs + i) + 1]) / (xn + eps);
   }
   return Status::ok();
 }

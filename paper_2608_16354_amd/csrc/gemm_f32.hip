@@ -31,12 +31,29 @@ __device__ inline float silu(float z) { return z / (1.0f + expf(-z)); }
 
 // Epilogues: load(m, n) fetches what the result is added to (all of a lane's loads go out
 // before its first store), store(m, n, acc, loaded) writes one element.
+// With bias_rows, rows from there on (the tangents stacked below a primal activation) get no bias.
 struct EpiBiasAct {
   const float* bias; float* out; int ldo; int act;
   __device__ float load(int, int) const { return 0.f; }
   __device__ void store(int m, int n, float v, float) const {
     v += bias[n];
     out[size_t(m) * ldo + n] = act ? silu(v) : v;
+  }
+};
+struct EpiBiasRows {
+  const float* bias; float* out; int ldo; int bias_rows;
+  __device__ float load(int, int) const { return 0.f; }
+  __device__ void store(int m, int n, float v, float) const {
+    out[size_t(m) * ldo + n] = m < bias_rows ? v + bias[n] : v;
+  }
+};
+struct EpiBiasAndSilu {
+  const float* bias; float* out; float* silu_out; int ldo;
+  __device__ float load(int, int) const { return 0.f; }
+  __device__ void store(int m, int n, float v, float) const {
+    v += bias[n];
+    out[size_t(m) * ldo + n] = v;
+    silu_out[size_t(m) * ldo + n] = silu(v);
   }
 };
 struct EpiGelu {
@@ -49,6 +66,13 @@ struct EpiGateResidual {
   __device__ float load(int m, int n) const { return h[size_t(m) * ldh + n]; }
   __device__ void store(int m, int n, float v, float old) const {
     h[size_t(m) * ldh + n] = old + gate[n] * (v + bias[n]);
+  }
+};
+struct EpiGateResidualRows {
+  const float* bias; const float* gate; float* h; int ldh; int bias_rows;
+  __device__ float load(int m, int n) const { return h[size_t(m) * ldh + n]; }
+  __device__ void store(int m, int n, float v, float old) const {
+    h[size_t(m) * ldh + n] = old + gate[n] * (m < bias_rows ? v + bias[n] : v);
   }
 };
 struct EpiPatch {
@@ -67,6 +91,15 @@ struct EpiHeadEuler {
   }
   __device__ float load(int m, int n) const { return x[at(m, n)]; }
   __device__ void store(int m, int n, float v, float old) const { x[at(m, n)] = old + dsigma * (v + bias[n]); }
+};
+// the same for tangents: row m = token m % N of tangent m / N, tokens from Nv on (text) have no
+// output, no bias; x: one latent of `lat` elements per tangent
+struct EpiHeadTangents {
+  EpiHeadEuler e; int N, Nv; size_t lat;
+  __device__ float load(int m, int n) const { return e.x[size_t(m / N) * lat + e.at(min(m % N, Nv - 1), n)]; }
+  __device__ void store(int m, int n, float v, float old) const {
+    if (m % N < Nv) e.x[size_t(m / N) * lat + e.at(m % N, n)] = old + e.dsigma * v;
+  }
 };
 
 // four consecutive weights as fp32
@@ -326,9 +359,9 @@ Status gemm_f32_bias_act(const float* A, int lda, const float* W, int ldw, const
   return gemm(A, lda, W, ldw, M, N, K, EpiBiasAct{bias, out, ldo, act == Act::kSilu ? 1 : 0}, s);
 }
 
-Status gemm_f32_bias_act(const float* A, int lda, const uint16_t* W, int ldw, const float* bias,
-                         float* out, int ldo, int M, int N, int K, Act act, hipStream_t s) {
-  return gemm(A, lda, W, ldw, M, N, K, EpiBiasAct{bias, out, ldo, act == Act::kSilu ? 1 : 0}, s);
+Status gemm_f32_bias_and_silu(const float* A, int lda, const float* W, int ldw, const float* bias,
+                              float* out, float* silu_out, int ldo, int M, int N, int K, hipStream_t s) {
+  return gemm(A, lda, W, ldw, M, N, K, EpiBiasAndSilu{bias, out, silu_out, ldo}, s);
 }
 
 Status gemm_f32_gate_residual(const float* A, int lda, const float* W, int ldw, const float* bias,
@@ -337,10 +370,27 @@ Status gemm_f32_gate_residual(const float* A, int lda, const float* W, int ldw, 
   return gemm(A, lda, W, ldw, M, N, K, EpiGateResidual{bias, gate, h, ldh}, s);
 }
 
-Status gemm_f32_gate_residual(const float* A, int lda, const uint16_t* W, int ldw, const float* bias,
-                              const float* gate, float* h, int ldh, int M, int N, int K,
-                              hipStream_t s) {
-  return gemm(A, lda, W, ldw, M, N, K, EpiGateResidual{bias, gate, h, ldh}, s);
+Status gemm_f32_rows(const float* A, int lda, const void* W, bool w_bf16, int ldw, const float* bias,
+                     int bias_rows, float* out, int ldo, int M, int N, int K, hipStream_t s) {
+  const EpiBiasRows e{bias, out, ldo, bias_rows};
+  if (w_bf16) return gemm(A, lda, static_cast<const uint16_t*>(W), ldw, M, N, K, e, s);
+  return gemm(A, lda, static_cast<const float*>(W), ldw, M, N, K, e, s);
+}
+
+Status gemm_f32_gate_residual_rows(const float* A, int lda, const void* W, bool w_bf16, int ldw,
+                                   const float* bias, int bias_rows, const float* gate, float* h, int ldh,
+                                   int M, int N, int K, hipStream_t s) {
+  const EpiGateResidualRows e{bias, gate, h, ldh, bias_rows};
+  if (w_bf16) return gemm(A, lda, static_cast<const uint16_t*>(W), ldw, M, N, K, e, s);
+  return gemm(A, lda, static_cast<const float*>(W), ldw, M, N, K, e, s);
+}
+
+Status gemm_f32_head_tangents(const float* A, const void* W, bool w_bf16, float* x, float dsigma,
+                              const Geo& g, int n, hipStream_t s) {
+  const EpiHeadTangents e{{nullptr, x, dsigma, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp}, g.N, g.Nv,
+                          size_t(g.C) * g.T * g.Hl * g.Wl};
+  if (w_bf16) return gemm(A, g.d, static_cast<const uint16_t*>(W), g.d, n * g.N, g.P, g.d, e, s);
+  return gemm(A, g.d, static_cast<const float*>(W), g.d, n * g.N, g.P, g.d, e, s);
 }
 
 Status gemm_f32_gelu(const float* A, int lda, const float* W, int ldw, const float* bias, float* out,
@@ -354,11 +404,6 @@ Status gemm_f32_patch_embed(const float* A, const float* W, const float* bias, c
 }
 
 Status gemm_f32_head(const float* A, int lda, const float* W, const float* bias, float* x,
-                     float dsigma, const Geo& g, int M, hipStream_t s) {
-  return gemm(A, lda, W, g.d, M, g.P, g.d, EpiHeadEuler{bias, x, dsigma, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp}, s);
-}
-
-Status gemm_f32_head(const float* A, int lda, const uint16_t* W, const float* bias, float* x,
                      float dsigma, const Geo& g, int M, hipStream_t s) {
   return gemm(A, lda, W, g.d, M, g.P, g.d, EpiHeadEuler{bias, x, dsigma, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp}, s);
 }

@@ -96,10 +96,10 @@ Status make_idx(const int32_t* idx, int32_t n, IdxList& out);
 struct Workspace {
   size_t a, qk, vt, o, ff, patch, drift_part, attn_part, attn_part_bytes, tm_e, tm_h, tm_c, tm_s, tm_m, total;
   int ldv;               // row stride of the transposed value buffer (tokens, padded)
-  int kTmax;             // steps the modulation scratch can hold per pass
 };
 Workspace workspace_layout(const Geo& g, int batch);
 
+constexpr int kModSteps = 64;       // denoising steps per pass of the modulation
 constexpr int kDriftBlocks = 1024;  // fixed grid per sample: reproducible reductions
 
 // Compute units of the current device (looked up once per device); 0 if there is none.
@@ -113,6 +113,9 @@ enum class Act { kNone, kSilu };
 // fp32 GEMM, C = A W^T (+ epilogue).  A [M, K] (lda), W [N, K] (ldw); K % 64 == 0.
 Status gemm_f32_bias_act(const float* A, int lda, const float* W, int ldw, const float* bias,
                          float* out, int ldo, int M, int N, int K, Act act, hipStream_t s);
+// out = A W^T + bias and silu_out = SiLU(out)
+Status gemm_f32_bias_and_silu(const float* A, int lda, const float* W, int ldw, const float* bias,
+                              float* out, float* silu_out, int ldo, int M, int N, int K, hipStream_t s);
 Status gemm_f32_gate_residual(const float* A, int lda, const float* W, int ldw, const float* bias,
                               const float* gate, float* h, int ldh, int M, int N, int K,
                               hipStream_t s);
@@ -122,15 +125,16 @@ Status gemm_f32_patch_embed(const float* A, const float* W, const float* bias, c
                             float* out, int ldo, int M, int N, hipStream_t s);
 Status gemm_f32_head(const float* A, int lda, const float* W, const float* bias, float* x,
                      float dsigma, const Geo& g, int M, hipStream_t s);
-// the same fp32 GEMMs with bf16 weights (bits widened exactly on load): the tangent
-// passes of the calibration on bf16 models
-Status gemm_f32_bias_act(const float* A, int lda, const uint16_t* W, int ldw, const float* bias,
-                         float* out, int ldo, int M, int N, int K, Act act, hipStream_t s);
-Status gemm_f32_gate_residual(const float* A, int lda, const uint16_t* W, int ldw, const float* bias,
-                              const float* gate, float* h, int ldh, int M, int N, int K,
-                              hipStream_t s);
-Status gemm_f32_head(const float* A, int lda, const uint16_t* W, const float* bias, float* x,
-                     float dsigma, const Geo& g, int M, hipStream_t s);
+// The calibration's GEMMs: rows from bias_rows on (tangents stacked below a primal activation)
+// get no bias; weights fp32, or bf16 (w_bf16) widened exactly on load.
+Status gemm_f32_rows(const float* A, int lda, const void* W, bool w_bf16, int ldw, const float* bias,
+                     int bias_rows, float* out, int ldo, int M, int N, int K, hipStream_t s);
+Status gemm_f32_gate_residual_rows(const float* A, int lda, const void* W, bool w_bf16, int ldw,
+                                   const float* bias, int bias_rows, const float* gate, float* h, int ldh,
+                                   int M, int N, int K, hipStream_t s);
+// n tangents da [n, N, d] through the head: x [n, latent] += dsigma unpatchify(da[:, :Nv] W^T)
+Status gemm_f32_head_tangents(const float* A, const void* W, bool w_bf16, float* x, float dsigma,
+                              const Geo& g, int n, hipStream_t s);
 
 // bf16 MFMA GEMM variants.
 Status gemm_bf16_qkv(const uint16_t* A, const uint16_t* W, const float* bias, uint16_t* qk,
@@ -176,29 +180,42 @@ Status drift_noalloc(const float* h_in, const float* mod0, void* u_ref, bool sna
                      const IdxList& idx, const Geo& g, hipStream_t s);
 Status patchify(const float* x, float* patches, const Geo& g, hipStream_t s);
 
-// Anchor calibration (Eq. 5-7): tangent-mode kernels of the fp32 network (calib.hip) and
-// the driver (calib.cpp).  a = LN(x)(1+scale)+shift and da its tangent along dx, per row;
-// o, dout = attention over qkv [M, 3d] and its tangent along dqkv; z, dz <- GELU(z) and
-// its tangent; out = alpha x + beta y (y may be NULL); sumsq -> out2 = (sum (a-b)^2, sum a^2)
-// (b may be NULL) in a fixed order, with sumsq_scratch_doubles() doubles of scratch.
-Status ln_mod_jvp(const float* x, const float* dx, int rows, int ld, int d, const float* shift,
-                  const float* scale, float* a, float* da, float eps, hipStream_t s);
-Status attention_jvp_f32(const float* qkv, const float* dqkv, const Geo& g, int M, float* o,
-                         float* dout, hipStream_t s);
-Status gelu_jvp(float* z, float* dz, size_t n, hipStream_t s);
+// Anchor calibration (Eq. 5-7): tangent-mode kernels of the fp32 network (calib.hip) and the
+// driver (calib.cpp).  Activations are stacked: the primal [rows], then n tangents [rows] each.
+constexpr int kMaxTangents = 32;
+// per row of the stack [1 + n, rows, d]: a = LN(x)(1+scale)+shift and its n tangents
+Status ln_mod_jvp(const float* x, int n, int rows, int d, const float* shift, const float* scale, float* a,
+                  float eps, hipStream_t s);
+// qkv [1 + n, M, 3d] -> o [1 + n, M, d]: attention and its n tangents (attention_f32.hip)
+Status attention_jvp_f32(const float* qkv, int n, const Geo& g, int M, float* o, hipStream_t s);
+// z [1 + n, count] <- GELU(z) and its n tangents
+Status gelu_jvp(float* z, int n, size_t count, hipStream_t s);
+// patches [n, N, 64] of n latents dx (text rows zero)
+Status patchify_tangents(const float* dx, float* patches, const Geo& g, int n, hipStream_t s);
+// out[i] [Nv, d] (stride `stride`) = x + r[i], i < n <= kMaxTangents + 1; r: host array of device pointers
+Status add_each(const float* x, const float* const* r, int n, size_t count, float* out, size_t stride,
+                hipStream_t s);
+// out = alpha x + beta y
 Status lincomb(float* out, const float* x, float alpha, const float* y, float beta, size_t n,
                hipStream_t s);
+// out = alpha (x - y)
+Status scaled_diff(float* out, const float* x, const float* y, float alpha, size_t n, hipStream_t s);
+// out2[i] = (sum (a[i]-b[i])^2, sum a[i]^2) for i < count (b[i] may be NULL) in a fixed order, with
+// sumsq_scratch_doubles() doubles of scratch; a, b: host arrays of device pointers
 size_t sumsq_scratch_doubles();
-Status sumsq(const float* a, const float* b, size_t n, double* scratch, double* out2, hipStream_t s);
+Status sumsq(const float* const* a, const float* const* b, int count, size_t n, double* scratch, double* out2,
+             hipStream_t s);
 size_t calibrate_workspace_bytes(const Geo& g, int K);
 Status calibrate_tables(const Geo& g, const dc_model_weights* w, const float* x1, const float* txt,
                         const double* sigmas, int K, int h_max, double eps, double* q, double* dtab,
                         void* ws, size_t ws_bytes, hipStream_t s);
 Status copy_text(const float* txt, float* h_in, const Geo& g, hipStream_t s);
 Status copy_rows(const float* src, float* dst, size_t count, hipStream_t s);
+// e [K, n_freq] from the host noise levels (K <= kModSteps)
 Status time_features(const double* sig, int K, float* e, int n_freq, hipStream_t s);
-Status silu_inplace(const float* in, float* out, size_t n, hipStream_t s);
-Status assemble_modulation(const float* m, const float* c, const float* offset, int K, int L,
-                           int l, const Geo& g, float* mod, int k0, hipStream_t s);
+// mod [K, L+1, 6, d] from m [K, 6, d], c [K, d], the L per-block offsets (host array of device
+// pointers) and the head's offset
+Status assemble_modulation(const float* m, const float* c, const float* const* offsets,
+                           const float* head_mod, int K, const Geo& g, float* mod, hipStream_t s);
 
 }  // namespace dc

@@ -263,42 +263,46 @@ __global__ void k_copy4(const float4* __restrict__ src, float4* __restrict__ dst
     dst[i] = src[i];
 }
 
+// Up to 64 noise levels or device pointers, passed to a kernel by value.
+struct Sigmas { double v[kModSteps]; };
+constexpr int kModBlocks = 64;
+struct Offsets { const float* p[kModBlocks]; };
+
 // e[k] = [cos(t w_i), sin(t w_i)], t = 1000 sigma_k, w_i = 10000^(-i/half); in double.
-__global__ void k_time_features(const double* __restrict__ sig, int K, float* __restrict__ e,
-                                int n_freq) {
+__global__ void k_time_features(Sigmas sig, float* __restrict__ e, int n_freq) {
   const int half = n_freq / 2;
   const int k = blockIdx.x;
   for (int i = threadIdx.x; i < half; i += blockDim.x) {
     const double w = exp(-double(i) / double(half) * log(10000.0));
-    const double arg = 1000.0 * sig[k] * w;
+    const double arg = 1000.0 * sig.v[k] * w;
     e[size_t(k) * n_freq + i] = float(cos(arg));
     e[size_t(k) * n_freq + half + i] = float(sin(arg));
   }
 }
 
-__global__ void k_silu(const float* __restrict__ in, float* __restrict__ out, size_t n) {
-  for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += size_t(gridDim.x) * blockDim.x) {
-    const float v = in[i];
-    out[i] = v / (1.0f + expf(-v));
+// mod[k0 + k, l] = m[k] (6 rows) + offset_l for the nl blocks from l0 on; with head, also
+// mod[k0 + k, L] = (head_mod + c[k] in rows 0, 1; zeros).  A thread keeps four elements of m[k]
+// and writes them for every block, so the table (71 MB for 50 steps x 30 blocks of 1,920) is
+// one pass of 16-byte stores and one launch: 31 launches of one block each took 106 us.
+__global__ void __launch_bounds__(256) k_assemble(const float4* __restrict__ m, const float4* __restrict__ c,
+                                                  Offsets off, const float4* __restrict__ head_mod,
+                                                  int nl, int l0, int L, int d4, int head,
+                                                  float4* __restrict__ mod) {
+  const int k = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= 6 * d4) return;
+  float4* dst = mod + size_t(k) * (L + 1) * 6 * d4 + e;
+  const float4 v = m[size_t(k) * 6 * d4 + e];
+  for (int l = 0; l < nl; ++l) {
+    const float4 o = reinterpret_cast<const float4*>(off.p[l])[e];
+    dst[size_t(l0 + l) * 6 * d4] = make_float4(v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w);
   }
-}
-
-// mod[k0+k, l] = m[k] (6 rows) + offset (block l < L); for l == L rows 0, 1 = offset + c[k].
-__global__ void k_assemble(const float* __restrict__ m, const float* __restrict__ c,
-                           const float* __restrict__ offset, int L, int l, int d,
-                           float* __restrict__ mod, int k0) {
-  const int k = blockIdx.y;
-  float* dst = mod + (size_t(k0 + k) * (L + 1) + l) * 6 * d;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < 6 * d; e += gridDim.x * blockDim.x) {
-    float v;
-    if (l < L) {
-      v = m[size_t(k) * 6 * d + e] + offset[e];
-    } else {
-      const int r = e / d;
-      v = (r < 2) ? offset[e] + c[size_t(k) * d + (e % d)] : 0.0f;
+  if (head) {
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (e < 2 * d4) {
+      const float4 o = head_mod[e], q = c[size_t(k) * d4 + (e < d4 ? e : e - d4)];
+      r = make_float4(o.x + q.x, o.y + q.y, o.z + q.z, o.w + q.w);
     }
-    dst[e] = v;
+    dst[size_t(L) * 6 * d4] = r;
   }
 }
 
@@ -406,22 +410,27 @@ Status copy_text(const float* txt, float* h_in, const Geo& g, hipStream_t s) {
 }
 
 Status time_features(const double* sig, int K, float* e, int n_freq, hipStream_t s) {
-  hipLaunchKernelGGL(k_time_features, dim3(K), dim3(128), 0, s, sig, K, e, n_freq);
+  if (K < 1 || K > kModSteps) return Status::arg("time_features: too many steps");
+  Sigmas a{};
+  for (int k = 0; k < K; ++k) a.v[k] = sig[k];
+  hipLaunchKernelGGL(k_time_features, dim3(K), dim3(128), 0, s, a, e, n_freq);
   DC_LAUNCH_CHECK();
   return Status::ok();
 }
 
-Status silu_inplace(const float* in, float* out, size_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_silu, dim3(grid_for(n, 256, 1024)), dim3(256), 0, s, in, out, n);
-  DC_LAUNCH_CHECK();
-  return Status::ok();
-}
-
-Status assemble_modulation(const float* m, const float* c, const float* offset, int K, int L,
-                           int l, const Geo& g, float* mod, int k0, hipStream_t s) {
-  hipLaunchKernelGGL(k_assemble, dim3(grid_for(size_t(6) * g.d, 256, 64), K), dim3(256), 0, s, m,
-                     c, offset, L, l, g.d, mod, k0);
-  DC_LAUNCH_CHECK();
+Status assemble_modulation(const float* m, const float* c, const float* const* offsets,
+                           const float* head_mod, int K, const Geo& g, float* mod, hipStream_t s) {
+  const int d4 = g.d / 4;
+  for (int l0 = 0; l0 < g.L; l0 += kModBlocks) {
+    const int nl = std::min(kModBlocks, g.L - l0);
+    Offsets off{};
+    for (int l = 0; l < nl; ++l) off.p[l] = offsets[l0 + l];
+    hipLaunchKernelGGL(k_assemble, dim3((6 * d4 + 255) / 256, K), dim3(256), 0, s,
+                       reinterpret_cast<const float4*>(m), reinterpret_cast<const float4*>(c), off,
+                       reinterpret_cast<const float4*>(head_mod), nl, l0, g.L, d4, l0 + nl == g.L ? 1 : 0,
+                       reinterpret_cast<float4*>(mod));
+    DC_LAUNCH_CHECK();
+  }
   return Status::ok();
 }
 

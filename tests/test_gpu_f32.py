@@ -60,13 +60,14 @@ def test_block_forward_f32(api, dev, name):
     assert err_h < 4e-6 and err_d < 4e-6
 
 
-@pytest.mark.parametrize("lat,n_txt", [((1, 6, 10), 0), ((3, 10, 12), 5)])
+@pytest.mark.parametrize("lat,n_txt", [((1, 6, 10), 0), ((3, 10, 12), 5), ((5, 28, 40), 1)])
 def test_calibration_at_ragged_token_counts(api, dev, lat, n_txt):
-    """15 tokens (less than one tile) and 95 (ragged), one refresh of each run length."""
+    """15 tokens (less than one tile), 95 (ragged; 21 runs in one group of tangents) and 1,401
+    (two tangents per group, several groups)."""
     import torch
     m = _shape(256, lat, n_txt, n_blocks=2)
     W = I.Weights(m, 121)
-    K, h_max = 4, 2
+    K, h_max = (8, 5) if m.n_tok == 95 else (4, 2)
     x1, txt = I.latent(m, 121, 0), I.text(m, 121, 0)
     say("calibration N =", m.n_tok)
     q, d = api.dc_calibrate_tables(api.DeviceModel(W, dev), torch.from_numpy(x1).to(dev),
@@ -75,6 +76,24 @@ def test_calibration_at_ragged_token_counts(api, dev, lat, n_txt):
     qo, do = cal.run_tables(tr, h_max, 1e-6)
     assert np.array_equal(q == 0.0, qo == 0.0) and np.array_equal(d == 0.0, do == 0.0)
     assert np.allclose(q, qo, rtol=1e-5) and np.allclose(d, do, rtol=1e-6)
+
+
+def test_time_modulation_many_blocks(api, dev):
+    """65 blocks: one more than the offsets one launch of the table takes."""
+    import torch
+    m = _shape(128, (1, 4, 4), 0, n_blocks=65)
+    W = I.Weights(m, 123)
+    sig = np.array([0.9, 0.1])
+    mod = torch.full((2, m.n_blocks + 1, 6, m.hidden), 9.0, device=dev)
+    say("time_modulation, 65 blocks")
+    api.dc_time_modulation(api.DeviceModel(W, dev), sig, mod, api.Workspace(m, 1, dev))
+    torch.cuda.synchronize()
+    got = mod.cpu().numpy()
+    for k in range(2):
+        blocks, head = dit.step_modulation(dit.Params(W), sig[k])
+        for l in range(m.n_blocks):
+            assert rel_l2(got[k, l], blocks[l]) < 1e-5
+        assert rel_l2(got[k, m.n_blocks, :2], head) < 1e-5 and not got[k, m.n_blocks, 2:].any()
 
 
 @pytest.mark.parametrize("d,K", [(256, 1), (256, 17), (384, 40), (1024, 50), (768, 100), (128, 130)])
