@@ -1,8 +1,9 @@
 // Joint video + text self-attention, softmax(Q K^T / sqrt(d_h)) V per head, with
 // an online softmax (flash-style: the N x N score matrix never leaves registers).
 //
-// The bf16 model's kernels (the fp32 model's attention is in attention_f32.hip): k_attn16 (head_dim 64, sequences of 8,192 tokens and more; see its
-// own comment below) and k_attn_bf16 (head_dim 64 below that, and head_dim 72).
+// Three bf16 kernels (the fp32 model's attention is in attention_f32.hip): k_attn16 (head_dim 64,
+// many items), k_attn_keys (short sequences) and k_attn_bf16 (head_dim 64 between those, and
+// head_dim 72); which one is chosen at attention_bf16, the first two have comments of their own.
 //
 // k_attn_bf16 (gfx950 MFMA 32x32x16).  A workgroup is 4 waves x 32 query rows of one
 // head; key/value tiles of 64 tokens stream through a 3-stage LDS ring.  The QKV
@@ -386,7 +387,7 @@ __global__ void __launch_bounds__(256) k_attn_combine(const float* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// head_dim 64 on v_mfma_f32_16x16x32_bf16.  Same work items and tail split as
+// k_attn16: head_dim 64 on v_mfma_f32_16x16x32_bf16.  Same work items and tail split as
 // k_attn_bf16, but a two-stage K/V^T ring (32 KB of LDS, the next tile's DMA issued
 // right after the barrier that frees its stage) and at most 128 VGPRs, so four
 // workgroups (four waves per SIMD) are resident: 3 % faster at 17,776 tokens x 30
@@ -689,6 +690,363 @@ k_attn16(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, int l
   }
 }
 
+// ---------------------------------------------------------------------------
+// Short sequences: fewer items of 128 queries than compute units leave most of them idle and
+// one or two waves per SIMD on the rest (300 tokens x 30 heads: 90 items).  Here a workgroup
+// takes 64 queries of one head and its four waves are two query blocks of 32 times two wave
+// groups that take alternate key tiles and merge through LDS at the end: twice the
+// workgroups, half the serial chain over the keys.  Otherwise as k_attn16 (16x16x32 MFMAs,
+// -m as the C operand, the safe pass), with registers to spare at two waves per SIMD.
+// head_dim 64: K rows in natural order in LDS, read permuted; l is an all-ones MFMA.
+// head_dim 72: K rows stored permuted, 144 bytes each (conflict-free as it is), three 32-wide
+// steps of the score product with zeros in Q past the row; O^T has five 16-row blocks, of whose
+// last eight rows are used, and the ninth V^T row in LDS holds ones, so that row of O is l.
+// ---------------------------------------------------------------------------
+template <int D>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_attn_keys(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, int ldv,
+            uint16_t* __restrict__ out, int M, int d, int nqb, int items, int per_xcd) {
+  constexpr int BKV = 64, QW = 2, KS = 2, QR = 32 * QW;   // keys per tile, wave grid, queries
+  constexpr int KK = (D + 31) / 32;             // 32-wide steps of the score product
+  constexpr int DB = (D + 15) / 16;             // 16-row blocks of O^T
+  constexpr int KC = D / 8;                     // 16-byte chunks per K row
+  constexpr bool kOnesRow = D % 16 != 0;        // l comes with O (row D of V^T holds ones)
+  constexpr int TI = 8 / QW;                    // DMA instructions per wave, tile and operand
+  constexpr int KSLOT = BKV * KC, VSLOT = 16 * DB * 8, TILE = KSLOT + VSLOT;   // 16-byte slots
+  constexpr int STAGE = KS * TILE;
+  static_assert(D == 64 || D == 72, "64 slots more per operand at D = 72");
+  __shared__ uint4 lds[2 * STAGE];
+  __shared__ int redo;
+
+  const int w = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (w >= items) return;
+  const int te = (M + BKV - 1) / BKV;           // key tiles
+  const int head = w / nqb;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qw = wave % QW, ks = wave / QW;
+  const int c16 = lane & 15, g4 = lane >> 4;
+  const int q0 = (w - head * nqb) * QR + qw * 32;
+  const int ldq = 2 * d;
+  const uint16_t* Qb = qk + head * D;
+  const uint16_t* Kb = qk + d + head * D;
+  const uint16_t* Vb = vt + size_t(head) * D * ldv;
+  if (tid == 0) redo = 0;
+  if constexpr (kOnesRow) {
+    // V^T rows D .. 16 DB - 1 of every tile buffer: ones, then zeros (the DMA never writes them)
+    for (int e = tid; e < 2 * KS * (16 * DB - D) * 8; e += 256) {
+      const int b = e / ((16 * DB - D) * 8), r = e % ((16 * DB - D) * 8);
+      const uint32_t v = r < 8 ? 0x3F803F80u : 0u;
+      lds[b * TILE + KSLOT + D * 8 + r] = make_uint4(v, v, v, v);
+    }
+  }
+
+  // query fragments: lane holds Q[q0 + 16 qb + c16][32 kk + 8 g4 .. + 8]
+  bf16x8 qf[2][KK];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      const int q = q0 + 16 * qb + c16;
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (q < M && 32 * kk + 8 * g4 < D) v = *reinterpret_cast<const uint4*>(Qb + size_t(q) * ldq + 32 * kk + 8 * g4);
+      qf[qb][kk] = __builtin_bit_cast(bf16x8, v);
+    }
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+
+  // A DMA instruction fills 64 slots; each group fills its own tile of a stage, its two waves four
+  // instructions of K and of V^T each.  At head_dim 72 each operand has 64 slots more: wave
+  // 2 j takes those of tile j's K, wave 2 j + 1 those of its V^T.
+  auto k_off = [&](int slot) {                  // byte offset of a K slot from its tile's first row
+    const int r = D == 64 ? slot >> 3 : perm16(slot / KC);
+    const int c = D == 64 ? (slot & 7) ^ swz_k16(slot >> 3) : slot % KC;
+    return 2u * uint32_t(r * ldq + 8 * c);
+  };
+  auto v_off = [&](int slot) {
+    const int r = slot >> 3, c = (slot & 7) ^ swz_v(r);
+    return 2u * uint32_t(r * ldv + 8 * c);
+  };
+  uint32_t offK[TI], offV[TI], offX = 0;
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    offK[i] = k_off((qw * TI + i) * 64 + lane);
+    offV[i] = v_off((qw * TI + i) * 64 + lane);
+  }
+  if constexpr (D == 72) offX = wave & 1 ? v_off(512 + lane) : k_off(512 + lane);
+  auto issue = [&](uint4* stage, int t0) {      // tiles t0, t0 + 1 into a stage
+    const int t = t0 + ks;
+    if (t < te) {
+      uint4* sk = stage + ks * TILE;
+      const uint16_t* kt = Kb + size_t(t) * BKV * ldq;
+      const uint16_t* vtt = Vb + t * BKV;
+#pragma unroll
+      for (int i = 0; i < TI; ++i) dma16(kt, offK[i], sk + (qw * TI + i) * 64);
+#pragma unroll
+      for (int i = 0; i < TI; ++i) dma16(vtt, offV[i], sk + KSLOT + (qw * TI + i) * 64);
+    }
+    if constexpr (D == 72) {
+      const int j = wave >> 1, tx = t0 + j;
+      if (tx < te) {
+        uint4* sk = stage + j * TILE;
+        if (wave & 1) dma16(Vb + tx * BKV, offX, sk + KSLOT + 512);
+        else dma16(Kb + size_t(tx) * BKV * ldq, offX, sk + 512);
+      }
+    }
+  };
+
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = static_cast<__bf16>(1.0f);
+
+  f32x4 o[DB][2], lacc[kOnesRow ? 1 : 2], mneg[2];
+  float mrow[2];
+  bool fail = false;
+  // l of query block qb: every lane (ones MFMA), or lanes with g4 == (D % 16) / 4
+  auto l_of = [&](int qb) { return kOnesRow ? o[DB - 1][qb][0] : lacc[kOnesRow ? 0 : qb][0]; };
+
+  // one pass over the key tiles; safe: take the tile maximum on every tile
+  auto run = [&](bool safe) {
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      mrow[qb] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if constexpr (!kOnesRow) lacc[qb][i] = 0.f;
+        mneg[qb][i] = 0.f;
+      }
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[db][qb][i] = 0.f;
+    }
+    fail = false;
+
+    auto rescale = [&](int qb, float up) {      // m += up; O, l *= 2^-up
+      // (up < 0 only on the first tile, where O and l are zero and 2^-up may overflow)
+      const float a = __builtin_amdgcn_exp2f(fminf(-up, 0.f));
+      mrow[qb] += up;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if constexpr (!kOnesRow) lacc[qb][i] *= a;
+        mneg[qb][i] = -mrow[qb];
+      }
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[db][qb][i] *= a;
+    };
+
+    // scores of key block kb (16 keys) for both query blocks, with C = -m; with
+    // kMask the keys past M are set to -inf (the last tile only, so the common path
+    // is one branch-free block the scheduler can interleave).  Chunks past the row (D = 72)
+    // re-read its last one: Q is zero there.
+    auto scores = [&](const uint4* sk, int t, int kb, f32x4 (&sc)[2], auto kMask) {
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        bf16x8 kf;
+        if constexpr (D == 64) {
+          const int row = perm16(16 * kb + c16);
+          kf = __builtin_bit_cast(bf16x8, sk[row * 8 + ((4 * kk + g4) ^ swz_k16(row))]);
+        } else {
+          const int ch = 4 * kk + 3 < KC ? 4 * kk + g4 : min(4 * kk + g4, KC - 1);
+          kf = __builtin_bit_cast(bf16x8, sk[(16 * kb + c16) * KC + ch]);
+        }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+          sc[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[qb][kk], kk == 0 ? mneg[qb] : sc[qb], 0, 0, 0);
+      }
+      if constexpr (decltype(kMask)::value) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (t * BKV + perm16(16 * kb + 4 * g4 + i) >= M) {
+            sc[0][i] = -INFINITY;
+            sc[1][i] = -INFINITY;
+          }
+      }
+    };
+
+    // all scores of the tile, then per 32-key chunk: P = 2^(s - m) (bf16), O^T += V^T P^T,
+    // l += 1 P^T.  P of chunk c: keys 32 c + 8 g4 .. + 7 (blocks 2c and 2c+1, permuted rows)
+    auto body = [&](const uint4* sk, const uint4* sv, int t, auto kMask) {
+      f32x4 sb[4][2];
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) scores(sk, t, kb, sb[kb], kMask);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        bf16x8 pf[2];
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            pf[qb][e] = static_cast<__bf16>(__builtin_amdgcn_exp2f(sb[2 * c][qb][e]));
+            pf[qb][4 + e] = static_cast<__bf16>(__builtin_amdgcn_exp2f(sb[2 * c + 1][qb][e]));
+          }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          const int row = 16 * db + c16;
+          const bf16x8 vf = __builtin_bit_cast(bf16x8, sv[row * 8 + ((4 * c + g4) ^ swz_v(row))]);
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb)
+            o[db][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qb], o[db][qb], 0, 0, 0);
+        }
+        if constexpr (!kOnesRow) {
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb)
+            lacc[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[qb], lacc[qb], 0, 0, 0);
+        }
+      }
+    };
+
+    // one tile: the tile maximum (first tile, safe pass), P V and l, then the raise check
+    auto tile = [&](const uint4* sk, int t, auto kMask, bool domax, bool first) {
+      const uint4* sv = sk + KSLOT;
+      if (domax) {
+        // the tile maximum (a separate pass over the scores, which are recomputed below)
+        float mx[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+          f32x4 sc[2];
+          scores(sk, t, kb, sc, kMask);
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mx[qb] = fmaxf(mx[qb], sc[qb][i]);
+        }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+          float m = fmaxf(mx[qb], __shfl_xor(mx[qb], 16, 64));
+          m = fmaxf(m, __shfl_xor(m, 32, 64));
+          const float up = first ? m : fmaxf(m, 0.f);
+          if (up != 0.f) rescale(qb, up);
+        }
+      }
+      body(sk, sv, t, kMask);
+      // m lags the scores by more than about 58 (l >= 2^64, or l not finite): the item is
+      // redone in the safe pass.  While l < 2^64, every P and so O stay far inside the fp32
+      // range.
+      if (!safe) {
+        bool big = !(l_of(0) < 0x1p64f && l_of(1) < 0x1p64f);
+        if constexpr (kOnesRow) big = big && g4 == (D % 16) / 4;
+        // a real branch (not a select): it ends the tile's scheduling region, which keeps
+        // the compiler from interleaving tiles (that spills)
+        if (__builtin_amdgcn_ballot_w64(big) != 0) {
+          fail = true;
+          __builtin_amdgcn_s_sleep(0);
+        }
+      }
+    };
+    // two-stage ring: the stage's tiles have landed in every wave's view and every wave is done
+    // with the stage before, which then takes the KS tiles after
+    auto sync = [&](int t0, uint4* next) {
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      __builtin_amdgcn_s_barrier();
+      if (t0 + KS < te) issue(next, t0 + KS);
+    };
+    constexpr std::false_type kFull{};
+    constexpr std::true_type kPart{};
+    uint4* const s0 = lds;
+    uint4* const s1 = lds + STAGE;
+    // Step i takes tiles 2 i and 2 i + 1 from ring stage i % 2, one per group.  The first step and
+    // a last one with a partial or missing tile run outside the loop, so the loop body is
+    // one branch-free instance per stage.
+    const int nst = (te + KS - 1) / KS;
+    const bool ragged = nst * KS * BKV > M;           // the last step is not all full
+    const int nfl = ragged ? nst - 1 : nst;
+    const int off = ks * TILE;
+    issue(s0, 0);
+    sync(0, s1);
+    if (nfl > 0) tile(s0 + off, ks, kFull, true, true);
+    else if (ks < te) tile(s0 + off, ks, kPart, true, true);
+    for (int i = 1; i < nfl; i += 2) {
+      sync(i * KS, s0);
+      tile(s1 + off, i * KS + ks, kFull, safe, false);
+      if (i + 1 >= nfl) break;
+      sync((i + 1) * KS, s1);
+      tile(s0 + off, (i + 1) * KS + ks, kFull, safe, false);
+    }
+    if (ragged && nst > 1) {
+      const int i = nst - 1, t = i * KS + ks;
+      sync(i * KS, s0);                               // nothing left to prefetch
+      if (t < te) tile(lds + (i & 1) * STAGE + off, t, kPart, safe, false);   // one instance, stage by address
+    }
+  };
+
+  // pass 0 is the fast path; pass 1 (rare) redoes the item with the tile maximum on
+  // every tile when any wave saw a non-finite row sum (one call site: one inlined copy)
+  if constexpr (kOnesRow) __syncthreads();      // the ones rows are written
+  for (int pass = 0;; ++pass) {
+    run(pass > 0);
+    if (pass > 0) break;
+    if (__builtin_amdgcn_ballot_w64(fail) != 0 && lane == 0) redo = 1;
+    __syncthreads();
+    if (!redo) break;
+    __syncthreads();
+  }
+
+  // l in every lane
+  float l[2];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) l[qb] = kOnesRow ? __shfl(l_of(qb), 16 * ((D % 16) / 4) + c16, 64) : l_of(qb);
+
+  // group 1 leaves O, m and l in LDS (the tiles are done with), group 0 merges
+  constexpr int ROW = D + 4;
+  static_assert(size_t(QR) * ROW * 4 <= sizeof(lds), "merge space");
+  float* const mem = reinterpret_cast<float*>(lds);
+  __syncthreads();
+  if (ks > 0) {
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      float* rec = mem + (qw * 32 + 16 * qb + c16) * ROW;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+        if (16 * db + 4 * g4 < D)
+          *reinterpret_cast<float4*>(rec + 16 * db + 4 * g4) =
+              make_float4(o[db][qb][0], o[db][qb][1], o[db][qb][2], o[db][qb][3]);
+      if (g4 == 0) {
+        rec[D] = mrow[qb];
+        rec[D + 1] = l[qb];
+      }
+    }
+  }
+  __syncthreads();
+  if (ks > 0) return;
+  if (te > 1) {                                  // group 1 had a tile
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      const float* rec = mem + (qw * 32 + 16 * qb + c16) * ROW;
+      const float m1 = rec[D], m = fmaxf(mrow[qb], m1);
+      const float a0 = __builtin_amdgcn_exp2f(mrow[qb] - m), a1 = __builtin_amdgcn_exp2f(m1 - m);
+      l[qb] = l[qb] * a0 + rec[D + 1] * a1;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+        if (16 * db + 4 * g4 < D) {
+          const float4 x = *reinterpret_cast<const float4*>(rec + 16 * db + 4 * g4);
+          o[db][qb][0] = o[db][qb][0] * a0 + x.x * a1;
+          o[db][qb][1] = o[db][qb][1] * a0 + x.y * a1;
+          o[db][qb][2] = o[db][qb][2] * a0 + x.z * a1;
+          o[db][qb][3] = o[db][qb][3] * a0 + x.w * a1;
+        }
+    }
+  }
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const int q = q0 + 16 * qb + c16;
+    if (q >= M) continue;
+    const float inv = 1.0f / l[qb];
+    uint16_t* orow = out + size_t(q) * d + head * D;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      if (16 * db + 4 * g4 >= D) continue;
+      ushort4 v;
+      v.x = to_bf16(o[db][qb][0] * inv);
+      v.y = to_bf16(o[db][qb][1] * inv);
+      v.z = to_bf16(o[db][qb][2] * inv);
+      v.w = to_bf16(o[db][qb][3] * inv);
+      *reinterpret_cast<ushort4*>(orow + 16 * db + 4 * g4) = v;
+    }
+  }
+}
+
 }  // namespace
 
 // Resident workgroups of the bf16 attention kernel per XCD on the current device
@@ -707,8 +1065,6 @@ static int attn_slots_per_xcd() {
   }
   return cache[dev];
 }
-
-constexpr int kAttn16MinTokens = 8192;
 
 static int attn16_slots_per_xcd() {
   static int cache[64] = {0};
@@ -752,17 +1108,37 @@ static Status launch_attn(const uint16_t* qk, const uint16_t* vt, int ldv, uint1
   return Status::ok();
 }
 
+template <int D>
+static Status launch_keys(const uint16_t* qk, const uint16_t* vt, int ldv, uint16_t* out, const Geo& g, int M,
+                          hipStream_t s) {
+  const int nqb = (M + 63) / 64, items = nqb * g.H, per_xcd = (items + 7) / 8;
+  hipLaunchKernelGGL(k_attn_keys<D>, dim3(8 * per_xcd), dim3(256), 0, s, qk, vt, ldv, out, M, g.d, nqb, items,
+                     per_xcd);
+  DC_HIP(hipGetLastError());
+  return Status::ok();
+}
+
 Status attention_bf16(const uint16_t* qk, const uint16_t* vt, int ldv, uint16_t* out,
                       const Geo& g, int M, float* part, size_t part_bytes, hipStream_t s) {
   if (ldv % 64 || ldv < M) return Status::shape("attention needs ldv >= M, ldv % 64 == 0");
   // the padding tokens [M, ldv) of vt hold zeros: the bf16 QKV GEMM writes them
-  // head_dim 64: the 16x16x32 kernel from 8,192 tokens (MI355X, 17,776 x 30 heads: 1.96 vs
-  // 2.08 ms); below that its per-item first-tile pass costs more than it saves (3,597 x 30:
-  // 121 vs 119 us)
-  if (g.Dh == 64 && M >= kAttn16MinTokens) return launch_attn<64, true>(qk, vt, ldv, out, g, M, part, part_bytes, s);
-  if (g.Dh == 64) return launch_attn<64, false>(qk, vt, ldv, out, g, M, part, part_bytes, s);
+  if (g.Dh != 64 && g.Dh != 72) return Status::shape("bf16 attention supports head_dim 64 and 72");
+  const int64_t cus = compute_units();
+  if (cus <= 0) return Status::make(DC_ERR_HIP, "bf16 attention: no device");
+  // Which kernel (256 compute units, us, head_dim 64 unless noted):
+  //  - k_attn_keys while its items (64 queries of a head) are at most two per compute unit, from two
+  //    key tiles on: 300 tokens x 30 heads 6.8, k_attn_bf16 12.2; 1,556 x 20 (500 items) 18.9 and
+  //    34.5; head_dim 72, 2,000 x 16 (512) 29.2 and 38.2, 3,000 x 16 (752) 64.7 and 57.7;
+  //  - k_attn16 (head_dim 64) from 2.25 items of 128 queries per compute unit: 5,000 x 48 (1,920
+  //    items) 276, k_attn_bf16 304; 2,500 x 30 (600) 56.9 and 57.7; 5,000 x 12 (480) 87 and 80.5;
+  //    17,776 x 30 1,916 and 2,127;
+  //  - k_attn_bf16 between, and for head_dim 72.
+  if (M > 64 && int64_t(g.H) * ((M + 63) / 64) <= 2 * cus)
+    return g.Dh == 64 ? launch_keys<64>(qk, vt, ldv, out, g, M, s) : launch_keys<72>(qk, vt, ldv, out, g, M, s);
   if (g.Dh == 72) return launch_attn<72, false>(qk, vt, ldv, out, g, M, part, part_bytes, s);
-  return Status::shape("bf16 attention supports head_dim 64 and 72");
+  if (4 * int64_t(g.H) * ((M + 127) / 128) >= 9 * cus)
+    return launch_attn<64, true>(qk, vt, ldv, out, g, M, part, part_bytes, s);
+  return launch_attn<64, false>(qk, vt, ldv, out, g, M, part, part_bytes, s);
 }
 
 }  // namespace dc

@@ -17,7 +17,7 @@
 // carries the primal activations and every active tangent of the group, stacked as rows of the
 // same GEMMs.  T fills about 4,096 rows; one tangent at a time (the small fp32 model: 64 passes
 // of the network with its tangent, 2,900 launches, a wait per norm) took 15.5 ms, the groups
-// take 3.4 ms.  The norms are read back once, at the end.
+// take 3.7 ms.  The norms are read back once, at the end.
 // Runs with j + h > K price nothing and stay 0.  The trace runs the library's own
 // kernels for the model's dtype (bf16 models: bf16 MFMA blocks); r, u, the perturbations
 // and every tangent are fp32 (calib.hip and the fp32 GEMMs, with bf16 weights widened
