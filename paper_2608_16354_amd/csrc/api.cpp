@@ -156,20 +156,18 @@ Status patch_embed(const Geo& g, const dc_model_weights* w, const float* x, cons
   if (!w || !x || !h_in || (g.Nt > 0 && !txt)) return Status::arg("NULL argument");
   Workspace L;
   DC_TRY(check_ws(g, max_index(il) + 1, ws, ws_bytes, L));
+  if (il.n == 0) return Status::ok();
+  ProfScope ps(KClass::kPatchEmbed, s);
+  if (g.bf16)
+    return patch_embed_bf16(x, w->w_pe, w->b_pe, static_cast<const uint16_t*>(w->pos), txt, h_in, il, g, s);
   float* patches = at<float>(ws, L.patch);
   const size_t lat = size_t(g.C) * g.T * g.Hl * g.Wl;
   for (int i = 0; i < il.n; ++i) {
     const int b = il.v[i];
     float* hb = h_in + size_t(b) * g.N * g.d;
-    ProfScope ps(KClass::kPatchEmbed, s);
-    if (g.bf16) {
-      DC_TRY(patch_embed_bf16(x + size_t(b) * lat, w->w_pe, w->b_pe, static_cast<const uint16_t*>(w->pos),
-                              hb, g, s));
-    } else {
-      DC_TRY(patchify(x + size_t(b) * lat, patches, g, s));
-      DC_TRY(gemm_f32_patch_embed(patches, w->w_pe, w->b_pe, static_cast<const float*>(w->pos), hb, g.d, g.Nv,
-                                  g.d, s));
-    }
+    DC_TRY(patchify(x + size_t(b) * lat, patches, g, s));
+    DC_TRY(gemm_f32_patch_embed(patches, w->w_pe, w->b_pe, static_cast<const float*>(w->pos), hb, g.d, g.Nv,
+                                g.d, s));
     if (g.Nt > 0) DC_TRY(copy_text(txt + size_t(b) * g.Nt * g.d, hb, g, s));
   }
   return Status::ok();

@@ -9,8 +9,7 @@
 // bf16 head + Euler for models wider than the one-pass head kernel takes (d > 2048):
 // the same LDS-DMA GEMM with a 64 x 64 tile (N = 64 outputs) and the unpatchify +
 // Euler epilogue, after LN-modulation to bf16 rows.
-// bf16 patch embedding: fp32-accurate split-bf16 MFMA with the patchify gather fused.
-// (fp32 GEMMs: gemm_f32.hip.)
+// (fp32 GEMMs: gemm_f32.hip; bf16 patch embedding: patch_embed.hip.)
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -638,137 +637,6 @@ Status block_gemm(const uint16_t* A, int lda, const uint16_t* W, int ldw, int M,
   }
 }
 
-// ---------------------------------------------------------------------------
-// Patch embedding for the bf16 model: h_in[n] = patch(x)[n] W_pe^T + b + pos[n]
-// with the fp32 latent and fp32 W_pe kept at fp32 accuracy on bf16 MFMA: each
-// operand is split v = hi + lo (hi = bf16(v), lo = bf16(v - hi)) and the
-// product is hi*Whi + lo*Whi + hi*Wlo (the dropped lo*Wlo is ~2^-18 relative).
-// The patchify gather is fused: each lane reads its 8 patch-vector entries
-// straight from the latent.  A workgroup = 8 waves x 32 tokens x a 128-wide
-// column chunk; the chunk of W_pe is split once into LDS and shared.  Work items
-// (token block, column chunk) are dealt so that an XCD runs every column chunk of
-// a contiguous range of token blocks, so each XCD's L2 fetches only its own part
-// of the latent.  Each wave's 32 x 32 result tiles go through LDS, so the output
-// rows leave as 16-byte stores (8 rows x 128 bytes per instruction; ordinary stores:
-// the drift check and the first block read h_in right after, partly from the caches)
-// and the positional rows arrive as 8-byte loads.
-// ---------------------------------------------------------------------------
-struct PatchGeo { int T, Hl, Wl, p, lp, Hp, Wp; };   // lp = log2(p)
-
-constexpr int kPeStride = 40;   // floats per row of a wave's 32 x 32 result tile in LDS
-
-__global__ void __launch_bounds__(512) k_patch_embed_bf16(const float* __restrict__ x,
-                                                          const float* __restrict__ W,
-                                                          const float* __restrict__ bias,
-                                                          const uint16_t* __restrict__ pos,
-                                                          float* __restrict__ out, int Nv, int d,
-                                                          int items, int per_xcd, PatchGeo pg) {
-  __shared__ uint4 wh[128 * 8], wl[128 * 8];     // [n][16-byte chunk of k], swizzled
-  __shared__ __attribute__((aligned(16))) float res[8][32 * kPeStride];
-  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (item >= items) return;
-  const int ncc = d >> 7;
-  const int tb = item / ncc, cc = item - tb * ncc;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r32 = lane & 31, hi = lane >> 5;
-  const int n0 = cc * 128;
-  // stage W[n0 .. n0 + 128)[0 .. 64) as bf16 hi / lo: thread -> (row, 4 chunks of 4 k)
-  {
-    const int n = tid >> 2, k4 = (tid & 3) * 16;    // 16 consecutive k per thread
-    const float4* src = reinterpret_cast<const float4*>(W + size_t(n0 + n) * 64 + k4);
-    float4 v[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = src[q];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float f[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-      uint16_t h[4], l[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        h[j] = to_bf16(f[j]);
-        l[j] = to_bf16(f[j] - from_bf16(h[j]));
-      }
-      const int k = k4 + 4 * q;
-      const int e = n * 64 + ((k >> 3) ^ swz(n)) * 8 + (k & 7);   // bf16 index, 8-byte aligned
-      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(wh) + e) =
-          make_uint2(h[0] | (uint32_t(h[1]) << 16), h[2] | (uint32_t(h[3]) << 16));
-      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(wl) + e) =
-          make_uint2(l[0] | (uint32_t(l[1]) << 16), l[2] | (uint32_t(l[3]) << 16));
-    }
-  }
-  const int m0 = tb * 256 + wave * 32;
-  // epilogue role of a lane: rows 8 q + lane / 8 (q < 4) of a 32 x 32 tile, columns
-  // 4 (lane % 8) ..; the positional rows of the next tile are loaded one tile ahead
-  // (rows clamped into the table)
-  const int er = lane >> 3, ec = 4 * (lane & 7);
-  auto load_pos = [&](int tile, uint2 (&pv)[4], float4& b4) {
-    const int nc = n0 + 32 * tile + ec;
-    b4 = *reinterpret_cast<const float4*>(bias + nc);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      pv[q] = *reinterpret_cast<const uint2*>(pos + size_t(min(m0 + 8 * q + er, Nv - 1)) * d + nc);
-  };
-  uint2 pv[4];
-  float4 b4;
-  load_pos(0, pv, b4);
-  // A fragments: token m, patch-vector entries 16 kk + 8 hi + e
-  const int m = min(m0 + r32, Nv - 1);
-  const int t = m / (pg.Hp * pg.Wp), i = (m / pg.Wp) % pg.Hp, j = m % pg.Wp;
-  bf16x8 ah[4], al[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int q = 16 * kk + 8 * hi + e;
-      const int c = q >> (2 * pg.lp), a = (q >> pg.lp) & (pg.p - 1), b = q & (pg.p - 1);
-      const float v = x[((size_t(c) * pg.T + t) * pg.Hl + (pg.p * i + a)) * pg.Wl + (pg.p * j + b)];
-      const __bf16 h = static_cast<__bf16>(v);
-      ah[kk][e] = h;
-      al[kk][e] = static_cast<__bf16>(v - static_cast<float>(h));
-    }
-  __syncthreads();
-  float* const rt = res[wave];
-#pragma unroll
-  for (int tile = 0; tile < 4; ++tile) {
-    f32x16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    const int nr = 32 * tile + r32;                 // row of the LDS chunk
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int ch = (2 * kk + hi) ^ swz(nr);
-      const bf16x8 bh = __builtin_bit_cast(bf16x8, wh[nr * 8 + ch]);
-      const bf16x8 bl = __builtin_bit_cast(bf16x8, wl[nr * 8 + ch]);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[kk], bh, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[kk], bh, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[kk], bl, acc, 0, 0, 0);
-    }
-    const int nc = n0 + 32 * tile + ec;             // this lane's 4 output columns
-    uint2 pn[4];
-    float4 bn = b4;
-    if (tile < 3) load_pos(tile + 1, pn, bn);
-    // accumulator element r of lane (r32, hi): row 8 (r / 4) + 4 hi + r % 4, column r32
-#pragma unroll
-    for (int r = 0; r < 16; ++r) rt[(8 * (r >> 2) + 4 * hi + (r & 3)) * kPeStride + r32] = acc[r];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int mm = m0 + 8 * q + er;
-      const float4 a = *reinterpret_cast<const float4*>(rt + (8 * q + er) * kPeStride + ec);
-      float4 o;
-      o.x = (a.x + b4.x) + __uint_as_float(pv[q].x << 16);
-      o.y = (a.y + b4.y) + __uint_as_float(pv[q].x & 0xFFFF0000u);
-      o.z = (a.z + b4.z) + __uint_as_float(pv[q].y << 16);
-      o.w = (a.w + b4.w) + __uint_as_float(pv[q].y & 0xFFFF0000u);
-      if (mm < Nv) *reinterpret_cast<float4*>(out + size_t(mm) * d + nc) = o;
-    }
-    if (tile < 3) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) pv[q] = pn[q];
-      b4 = bn;
-    }
-  }
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -798,23 +666,6 @@ Status gemm_bf16_head(const uint16_t* A, int lda, const uint16_t* W, const float
   DC_TRY(check_gemm(lda, g.d, M, 64, g.d));
   EpiHeadEuler e{bias, x, dsigma, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp};
   return launch_dma<64, 64, 2, 2, 4, 2>(A, lda, W, g.d, M, 64, g.d, e, s);
-}
-
-Status patch_embed_bf16(const float* x, const float* W, const float* bias, const uint16_t* pos,
-                        float* out, const Geo& g, hipStream_t s) {
-  if (g.Nv <= 0) return Status::ok();
-  if (g.P != 64 || g.d % 128) return Status::shape("bf16 patch embedding needs 64-entry patches, d % 128 == 0");
-  int lp = 0;
-  while ((1 << lp) < g.p) ++lp;
-  if ((1 << lp) != g.p) return Status::shape("bf16 patch embedding needs a power-of-two patch");
-  if (!al16(out) || !al16(bias) || !al16(pos) || !al16(W))
-    return Status::arg("bf16 patch embedding needs 16-byte aligned device buffers");
-  const PatchGeo pg{g.T, g.Hl, g.Wl, g.p, lp, g.Hp, g.Wp};
-  const int items = (g.Nv + 255) / 256 * (g.d / 128), per_xcd = (items + 7) / 8;
-  hipLaunchKernelGGL(k_patch_embed_bf16, dim3(8 * per_xcd), dim3(512), 0, s, x, W, bias, pos, out,
-                     g.Nv, g.d, items, per_xcd, pg);
-  DC_HIP(hipGetLastError());
-  return Status::ok();
 }
 
 }  // namespace dc

@@ -145,8 +145,8 @@ Status gemm_bf16_gate_residual(const uint16_t* A, int lda, const uint16_t* W, co
 Status gemm_bf16_gelu(const uint16_t* A, int lda, const uint16_t* W, const float* bias,
                       uint16_t* out, int ldo, int M, int N, int K, hipStream_t s);
 // bf16 model: fused patchify + patch embedding (+ bias + positional table) for one sample.
-Status patch_embed_bf16(const float* x, const float* W, const float* bias, const uint16_t* pos,
-                        float* out, const Geo& g, hipStream_t s);
+Status patch_embed_bf16(const float* x, const float* W, const float* bias, const uint16_t* pos, const float* txt,
+                        float* out, const IdxList& idx, const Geo& g, hipStream_t s);
 Status gemm_bf16_head(const uint16_t* A, int lda, const uint16_t* W, const float* bias, float* x,
                       float dsigma, const Geo& g, int M, hipStream_t s);
 // bf16 model: LN-modulation + head projection + unpatchify + Euler update of one sample's
