@@ -233,13 +233,13 @@ Status block_forward(const Geo& g, const dc_block_weights* bw, const float* mod,
   return Status::ok();
 }
 
-// resid != NULL (bf16 models the fused head takes): the head input of sample b is
+// resid != NULL (where head_takes_resid): the head input of sample b is
 // g = gin[b] + resid[b] on the video rows, formed inside the head kernel (reuse steps).
 Status head_euler(const Geo& g, const dc_model_weights* w, const float* head_mod, const float* gin,
                   float* x, float dsigma, const IdxList& il, void* ws, size_t ws_bytes,
                   hipStream_t s, const void* resid) {
   if (!w || !head_mod || !gin || !x || !w->w_head || !w->b_head) return Status::arg("NULL argument");
-  if (resid && !head_euler_fused_ok(g)) return Status::shape("head with a residual input needs the fused bf16 head");
+  if (resid && !head_takes_resid(g)) return Status::shape("head with a residual input: bf16 and d <= 2048 only");
   Workspace L;
   DC_TRY(check_ws(g, max_index(il) + 1, ws, ws_bytes, L));
   const size_t lat = size_t(g.C) * g.T * g.Hl * g.Wl;
@@ -247,19 +247,15 @@ Status head_euler(const Geo& g, const dc_model_weights* w, const float* head_mod
     const int b = il.v[i];
     const float* gb = gin + size_t(b) * g.N * g.d;
     ProfScope ps(resid ? KClass::kHeadReuse : KClass::kHead, s);
-    if (head_euler_fused_ok(g)) {
+    if (g.bf16) {
       const uint16_t* rb = resid ? static_cast<const uint16_t*>(resid) + size_t(b) * g.Nv * g.d : nullptr;
       DC_TRY(head_euler_bf16(gb, rb, static_cast<const uint16_t*>(w->w_head), w->b_head, head_mod,
                              head_mod + g.d, x + size_t(b) * lat, dsigma, g, s));
       continue;
     }
-    DC_TRY(ln_modulate(gb, g.Nv, g.d, head_mod, head_mod + g.d, at<void>(ws, L.a), g.d, g.bf16, g, s));
-    if (g.bf16)
-      DC_TRY(gemm_bf16_head(at<uint16_t>(ws, L.a), g.d, static_cast<const uint16_t*>(w->w_head),
-                            w->b_head, x + size_t(b) * lat, dsigma, g, g.Nv, s));
-    else
-      DC_TRY(gemm_f32_head(at<float>(ws, L.a), g.d, static_cast<const float*>(w->w_head), w->b_head,
-                           x + size_t(b) * lat, dsigma, g, g.Nv, s));
+    DC_TRY(ln_modulate(gb, g.Nv, g.d, head_mod, head_mod + g.d, at<void>(ws, L.a), g.d, false, g, s));
+    DC_TRY(gemm_f32_head(at<float>(ws, L.a), g.d, static_cast<const float*>(w->w_head), w->b_head,
+                         x + size_t(b) * lat, dsigma, g, g.Nv, s));
   }
   return Status::ok();
 }

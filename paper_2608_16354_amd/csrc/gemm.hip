@@ -6,9 +6,6 @@
 // shapes, chosen per call by a cost model (block_gemm): long sequences take 384 x 192 or 320 x 256
 // (fewest operand lines per FLOP, the L1 miss queue being the limit there), short ones the
 // smaller tiles that spread over all compute units.
-// bf16 head + Euler for models wider than the one-pass head kernel takes (d > 2048):
-// the same LDS-DMA GEMM with a 64 x 64 tile (N = 64 outputs) and the unpatchify +
-// Euler epilogue, after LN-modulation to bf16 rows.
 // (fp32 GEMMs: gemm_f32.hip; bf16 patch embedding: patch_embed.hip.)
 #include <hip/hip_runtime.h>
 
@@ -206,40 +203,6 @@ struct EpiGeluBf16 {
       for (int i = 0; i < 16; ++i)
         if (mb + 8 * (i >> 2) + (i & 3) < M) o[size_t(8 * (i >> 2) + (i & 3)) * ldo] = to_bf16(gelu_tanh(v[i] + b));
     }
-  }
-};
-// Head + Euler: token m, patch-vector index n -> latent element; x += dsigma * (acc + b).
-struct EpiHeadEuler {
-  const float* bias; float* x; float dsigma; int T, Hl, Wl, p, Hp, Wp;
-  static constexpr int kRowVec = 0;                 // scattered latent writes: by column
-  __device__ bool isrow(int) const { return false; }
-  bool rows_aligned() const { return false; }
-  template <int NP>
-  __device__ void rows(int, int, int, int, const float (&)[NP][4]) const {}
-  __device__ float* at(int m, int n) const {
-    const int pp = p * p;
-    const int c = n / pp, a = (n / p) % p, b = n % p;
-    const int t = m / (Hp * Wp), i = (m / Wp) % Hp, j = m % Wp;
-    return x + ((size_t(c) * T + t) * Hl + (p * i + a)) * Wl + (p * j + b);
-  }
-  __device__ void col(int mb, int n, int M, const f32x16& v) const {
-    float a[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) a[i] = v[i];
-    col(mb, n, M, a);
-  }
-  // rows mb + 8 (i / 4) + i % 4 of output column n: all loads, then all stores
-  __device__ void col(int mb, int n, int M, const float (&v)[16]) const {
-    const float bn = bias[n];
-    float* dst[16];
-    float old[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) dst[i] = at(min(mb + 8 * (i >> 2) + (i & 3), M - 1), n);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) old[i] = *dst[i];
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (mb + 8 * (i >> 2) + (i & 3) < M) *dst[i] = old[i] + dsigma * (v[i] + bn);
   }
 };
 
@@ -657,15 +620,6 @@ Status gemm_bf16_gate_residual(const uint16_t* A, int lda, const uint16_t* W, co
 Status gemm_bf16_gelu(const uint16_t* A, int lda, const uint16_t* W, const float* bias,
                       uint16_t* out, int ldo, int M, int N, int K, hipStream_t s) {
   return block_gemm(A, lda, W, K, M, N, K, EpiGeluBf16{bias, out, ldo}, s);
-}
-
-Status gemm_bf16_head(const uint16_t* A, int lda, const uint16_t* W, const float* bias, float* x,
-                      float dsigma, const Geo& g, int M, hipStream_t s) {
-  if (M <= 0) return Status::ok();
-  if (g.P != 64 || g.d % 128 || lda % 8) return Status::shape("bf16 head needs 64 outputs and d % 128 == 0");
-  DC_TRY(check_gemm(lda, g.d, M, 64, g.d));
-  EpiHeadEuler e{bias, x, dsigma, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp};
-  return launch_dma<64, 64, 2, 2, 4, 2>(A, lda, W, g.d, M, 64, g.d, e, s);
 }
 
 }  // namespace dc

@@ -147,13 +147,11 @@ Status gemm_bf16_gelu(const uint16_t* A, int lda, const uint16_t* W, const float
 // bf16 model: fused patchify + patch embedding (+ bias + positional table) for one sample.
 Status patch_embed_bf16(const float* x, const float* W, const float* bias, const uint16_t* pos, const float* txt,
                         float* out, const IdxList& idx, const Geo& g, hipStream_t s);
-Status gemm_bf16_head(const uint16_t* A, int lda, const uint16_t* W, const float* bias, float* x,
-                      float dsigma, const Geo& g, int M, hipStream_t s);
 // bf16 model: LN-modulation + head projection + unpatchify + Euler update of one sample's
-// latent in one pass over its N_v video rows of g (head.hip); head_euler_fused_ok says
-// whether the shape is supported (64 outputs, d % 32 == 0, 256 <= d <= 2048).  With
-// resid != NULL the input is g = gin + resid (bf16), formed in registers (reuse steps).
-bool head_euler_fused_ok(const Geo& g);
+// latent in one pass over its N_v video rows of g (head.hip).  With resid != NULL the input
+// is g = gin + resid (bf16), formed in registers (reuse steps); head_takes_resid says whether
+// the model's width allows that.
+bool head_takes_resid(const Geo& g);
 Status head_euler_bf16(const float* gin, const uint16_t* resid, const uint16_t* W, const float* bias,
                        const float* shift, const float* scale, float* x, float dsigma, const Geo& g,
                        hipStream_t s);

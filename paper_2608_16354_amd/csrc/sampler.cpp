@@ -247,7 +247,7 @@ Status step(dc_sampler* s, int k, hipStream_t st, uint8_t* realized, double* dri
   }
   // reuse scenes: the fused bf16 head reads h_in and r itself; other models apply the
   // cache into h first
-  const bool fused_reuse = head_euler_fused_ok(g);
+  const bool fused_reuse = head_takes_resid(g);
   if (!reuse.empty() && !fused_reuse) {
     IdxList il;
     const std::vector<int32_t> rb = with_branches(reuse);
