@@ -87,7 +87,6 @@ Workspace workspace_layout(const Geo& g, int batch) {
   w.vt = take(size_t(g.d) * w.ldv * g.esz);
   w.o = take(size_t(g.N) * g.d * g.esz);
   w.ff = take(size_t(g.N) * g.F * g.esz);
-  w.patch = take(size_t(g.Nv) * 64 * 4);
   (void)batch;
   w.drift_part = take(size_t(DC_MAX_BATCH) * kDriftBlocks * 4 * sizeof(double));
   // split-tail partials of the bf16 attention: up to 64 split items per XCD, two halves of
@@ -160,17 +159,7 @@ Status patch_embed(const Geo& g, const dc_model_weights* w, const float* x, cons
   ProfScope ps(KClass::kPatchEmbed, s);
   if (g.bf16)
     return patch_embed_bf16(x, w->w_pe, w->b_pe, static_cast<const uint16_t*>(w->pos), txt, h_in, il, g, s);
-  float* patches = at<float>(ws, L.patch);
-  const size_t lat = size_t(g.C) * g.T * g.Hl * g.Wl;
-  for (int i = 0; i < il.n; ++i) {
-    const int b = il.v[i];
-    float* hb = h_in + size_t(b) * g.N * g.d;
-    DC_TRY(patchify(x + size_t(b) * lat, patches, g, s));
-    DC_TRY(gemm_f32_patch_embed(patches, w->w_pe, w->b_pe, static_cast<const float*>(w->pos), hb, g.d, g.Nv,
-                                g.d, s));
-    if (g.Nt > 0) DC_TRY(copy_text(txt + size_t(b) * g.Nt * g.d, hb, g, s));
-  }
-  return Status::ok();
+  return patch_embed_f32(x, w->w_pe, w->b_pe, static_cast<const float*>(w->pos), txt, h_in, il, g, s);
 }
 
 Status block_forward(const Geo& g, const dc_block_weights* bw, const float* mod, float* h,

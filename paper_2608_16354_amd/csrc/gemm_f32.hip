@@ -75,11 +75,6 @@ struct EpiGateResidualRows {
     h[size_t(m) * ldh + n] = old + gate[n] * (m < bias_rows ? v + bias[n] : v);
   }
 };
-struct EpiPatch {
-  const float* bias; const float* pos; float* out; int ldo;
-  __device__ float load(int m, int n) const { return pos[size_t(m) * ldo + n]; }
-  __device__ void store(int m, int n, float v, float p) const { out[size_t(m) * ldo + n] = (v + bias[n]) + p; }
-};
 // token m, patch-vector index n -> latent element; x += dsigma * (acc + b)
 struct EpiHeadEuler {
   const float* bias; float* x; float dsigma; int T, Hl, Wl, p, Hp, Wp;
@@ -396,11 +391,6 @@ Status gemm_f32_head_tangents(const float* A, const void* W, bool w_bf16, float*
 Status gemm_f32_gelu(const float* A, int lda, const float* W, int ldw, const float* bias, float* out,
                      int ldo, int M, int N, int K, hipStream_t s) {
   return gemm(A, lda, W, ldw, M, N, K, EpiGelu{bias, out, ldo}, s);
-}
-
-Status gemm_f32_patch_embed(const float* A, const float* W, const float* bias, const float* pos,
-                            float* out, int ldo, int M, int N, hipStream_t s) {
-  return gemm(A, 64, W, 64, M, N, 64, EpiPatch{bias, pos, out, ldo}, s);
 }
 
 Status gemm_f32_head(const float* A, int lda, const float* W, const float* bias, float* x,

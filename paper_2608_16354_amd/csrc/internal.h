@@ -94,7 +94,7 @@ Status make_idx(const int32_t* idx, int32_t n, IdxList& out);
 
 // Workspace layout (offsets in bytes, each 256-aligned).
 struct Workspace {
-  size_t a, qk, vt, o, ff, patch, drift_part, attn_part, attn_part_bytes, tm_e, tm_h, tm_c, tm_s, tm_m, total;
+  size_t a, qk, vt, o, ff, drift_part, attn_part, attn_part_bytes, tm_e, tm_h, tm_c, tm_s, tm_m, total;
   int ldv;               // row stride of the transposed value buffer (tokens, padded)
 };
 Workspace workspace_layout(const Geo& g, int batch);
@@ -121,8 +121,6 @@ Status gemm_f32_gate_residual(const float* A, int lda, const float* W, int ldw, 
                               hipStream_t s);
 Status gemm_f32_gelu(const float* A, int lda, const float* W, int ldw, const float* bias,
                      float* out, int ldo, int M, int N, int K, hipStream_t s);
-Status gemm_f32_patch_embed(const float* A, const float* W, const float* bias, const float* pos,
-                            float* out, int ldo, int M, int N, hipStream_t s);
 Status gemm_f32_head(const float* A, int lda, const float* W, const float* bias, float* x,
                      float dsigma, const Geo& g, int M, hipStream_t s);
 // The calibration's GEMMs: rows from bias_rows on (tangents stacked below a primal activation)
@@ -144,9 +142,12 @@ Status gemm_bf16_gate_residual(const uint16_t* A, int lda, const uint16_t* W, co
                                hipStream_t s);
 Status gemm_bf16_gelu(const uint16_t* A, int lda, const uint16_t* W, const float* bias,
                       uint16_t* out, int ldo, int M, int N, int K, hipStream_t s);
-// bf16 model: fused patchify + patch embedding (+ bias + positional table) for one sample.
+// h_in of the samples idx: patchify + patch embedding + bias + positions, and the text rows
+// (patch_embed.hip).
 Status patch_embed_bf16(const float* x, const float* W, const float* bias, const uint16_t* pos, const float* txt,
                         float* out, const IdxList& idx, const Geo& g, hipStream_t s);
+Status patch_embed_f32(const float* x, const float* W, const float* bias, const float* pos, const float* txt,
+                       float* out, const IdxList& idx, const Geo& g, hipStream_t s);
 // bf16 model: LN-modulation + head projection + unpatchify + Euler update of one sample's
 // latent in one pass over its N_v video rows of g (head.hip).  With resid != NULL the input
 // is g = gin + resid (bf16), formed in registers (reuse steps); head_takes_resid says whether
@@ -176,7 +177,6 @@ Status drift(const float* h_in, const float* mod0, void* u_ref, bool snapshot, d
 // drift() with the partial sums in the library's fixed per-GPU scratch array (no workspace)
 Status drift_noalloc(const float* h_in, const float* mod0, void* u_ref, bool snapshot, double* sums,
                      const IdxList& idx, const Geo& g, hipStream_t s);
-Status patchify(const float* x, float* patches, const Geo& g, hipStream_t s);
 
 // Anchor calibration (Eq. 5-7): tangent-mode kernels of the fp32 network (calib.hip) and the
 // driver (calib.cpp).  Activations are stacked: the primal [rows], then n tangents [rows] each.
@@ -207,7 +207,6 @@ size_t calibrate_workspace_bytes(const Geo& g, int K);
 Status calibrate_tables(const Geo& g, const dc_model_weights* w, const float* x1, const float* txt,
                         const double* sigmas, int K, int h_max, double eps, double* q, double* dtab,
                         void* ws, size_t ws_bytes, hipStream_t s);
-Status copy_text(const float* txt, float* h_in, const Geo& g, hipStream_t s);
 Status copy_rows(const float* src, float* dst, size_t count, hipStream_t s);
 // e [K, n_freq] from the host noise levels (K <= kModSteps)
 Status time_features(const double* sig, int K, float* e, int n_freq, hipStream_t s);

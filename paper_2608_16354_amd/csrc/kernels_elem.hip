@@ -242,21 +242,6 @@ __global__ void __launch_bounds__(256) k_drift_reduce(const double* __restrict__
   if (threadIdx.x < 4) sums[size_t(idx.v[blockIdx.x]) * 4 + threadIdx.x] = red[0][threadIdx.x];
 }
 
-// patches[n, c p^2 + a p + b] = x[c, t, p i + a, p j + b], n = (t Hp + i) Wp + j.
-__global__ void __launch_bounds__(256) k_patchify(const float* __restrict__ x,
-                                                  float* __restrict__ patches, int C, int T,
-                                                  int Hl, int Wl, int p, int Hp, int Wp, int Nv) {
-  const int P = C * p * p;
-  const size_t total = size_t(Nv) * P;
-  for (size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x; e < total;
-       e += size_t(gridDim.x) * blockDim.x) {
-    const int n = int(e / P), q = int(e % P);
-    const int c = q / (p * p), a = (q / p) % p, bb = q % p;
-    const int t = n / (Hp * Wp), i = (n / Wp) % Hp, j = n % Wp;
-    patches[e] = x[((size_t(c) * T + t) * Hl + (p * i + a)) * Wl + (p * j + bb)];
-  }
-}
-
 __global__ void k_copy4(const float4* __restrict__ src, float4* __restrict__ dst, size_t n4) {
   for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n4;
        i += size_t(gridDim.x) * blockDim.x)
@@ -388,14 +373,6 @@ Status drift(const float* h_in, const float* mod0, void* u_ref, bool snapshot, d
   return Status::ok();
 }
 
-Status patchify(const float* x, float* patches, const Geo& g, hipStream_t s) {
-  const size_t total = size_t(g.Nv) * g.P;
-  hipLaunchKernelGGL(k_patchify, dim3(grid_for(total, 256, 8192)), dim3(256), 0, s, x, patches,
-                     g.C, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp, g.Nv);
-  DC_LAUNCH_CHECK();
-  return Status::ok();
-}
-
 Status copy_rows(const float* src, float* dst, size_t count, hipStream_t s) {
   if (count == 0) return Status::ok();
   const size_t n4 = count / 4;
@@ -403,10 +380,6 @@ Status copy_rows(const float* src, float* dst, size_t count, hipStream_t s) {
                      reinterpret_cast<const float4*>(src), reinterpret_cast<float4*>(dst), n4);
   DC_LAUNCH_CHECK();
   return Status::ok();
-}
-
-Status copy_text(const float* txt, float* h_in, const Geo& g, hipStream_t s) {
-  return copy_rows(txt, h_in + size_t(g.Nv) * g.d, size_t(g.Nt) * g.d, s);
 }
 
 Status time_features(const double* sig, int K, float* e, int n_freq, hipStream_t s) {

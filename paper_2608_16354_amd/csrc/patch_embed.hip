@@ -1,8 +1,8 @@
-// Patch embedding of the bf16 model with the text rows, one launch for all samples:
+// Patch embedding with the text rows, one launch for all samples:
 //
 //   h_in[n] = patch(x)[n] W_pe^T + b + pos[n]  (n < N_v),   h_in[N_v + i] = txt[i]
 //
-// fp32 latent and fp32 W_pe at fp32 accuracy on bf16 MFMA: each operand is split v = hi + lo
+// bf16 model: fp32 latent and fp32 W_pe at fp32 accuracy on bf16 MFMA: each operand is split v = hi + lo
 // (hi = bf16(v), lo = bf16(v - hi)) and the product is hi*Whi + lo*Whi + hi*Wlo (the dropped
 // lo*Wlo is about 2^-18 relative).
 //
@@ -19,6 +19,10 @@
 // 3,704 x 1,152: 10.4 us, 18.  Before, a workgroup staged W in LDS for 256 tokens x 128 columns;
 // 1,035 of them on 512 slots took a third round for eleven, and the text rows were copied by a
 // launch of their own.
+//
+// fp32 model: v_mfma_f32_16x16x4_f32, 16 tokens x 32 columns a wave; calls of a few hundred
+// tokens, bound by launches and one chain of loads and 32 MFMAs.  256 tokens x 256: 4.9 us for what
+// took 2.9 + 3.8 + 1.5 in three launches (a sample of ten steps 973 -> 867 us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -226,7 +230,99 @@ k_patch_embed_bf16(const float* __restrict__ x, const float* __restrict__ W, con
     for (int s = s0; s < s1; ++s) step(s, std::false_type{});
 }
 
+// Lane (c16, g4) holds the entries 16 g4 + e (e < 16) of token c16 and of its two weight rows;
+// MFMA step e takes entry e on both sides.  Two chains of sums per tile.
+template <int V>
+__global__ void __launch_bounds__(kPeWaves * 64)
+k_patch_embed_f32(const float* __restrict__ x, const float* __restrict__ W, const float* __restrict__ bias,
+                  const float* __restrict__ pos, const float4* __restrict__ txt, float* __restrict__ out,
+                  IdxList idx, PatchGeo g) {
+  const int b = idx.v[blockIdx.y];
+  float* const ob = out + size_t(b) * g.h_stride;
+  if (int(blockIdx.x) >= g.items) {              // the workgroups past the strips copy the text rows
+    const size_t i = size_t(blockIdx.x - g.items) * (kPeWaves * 64) + threadIdx.x;
+    float4* dst = reinterpret_cast<float4*>(ob + size_t(g.Nv) * g.d);
+    if (i < g.txt4) dst[i] = txt[size_t(b) * g.txt4 + i];
+    return;
+  }
+  const int lane = threadIdx.x & 63, c16 = lane & 15, g4 = lane >> 4, wave = threadIdx.x >> 6;
+  const int t0 = int(blockIdx.x) / g.groups * kStrip;
+  const int nc = (int(blockIdx.x) % g.groups * kPeWaves + wave) * 32 + 2 * c16;   // two columns per lane
+  auto entry = [&](int q) {
+    const int c = q >> (2 * g.lp), a = (q >> g.lp) & (g.p - 1), bb = q & (g.p - 1);
+    return (size_t(c) * g.T * g.Hl + a) * g.Wl + bb;
+  };
+  const int m = min(t0 + c16, g.Nv - 1);
+  const int row = m / g.Wp, j = m - row * g.Wp, t = row / g.Hp, i = row - t * g.Hp;
+  const float* px = x + size_t(b) * g.latent + entry(16 * g4) + (size_t(t) * g.Hl + g.p * i) * g.Wl + g.p * j;
+  float v[16], w[2][16];
+#pragma unroll
+  for (int e = 0; e < 16; e += V) load_v<V>(px + entry(e), &v[e]);
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int e = 0; e < 16; e += 4) load_v<4>(W + size_t(nc + k) * 64 + 16 * g4 + e, &w[k][e]);
+  float2 pv[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    pv[r] = *reinterpret_cast<const float2*>(pos + size_t(min(t0 + 4 * g4 + r, g.Nv - 1)) * g.d + nc);
+  const float2 bv = *reinterpret_cast<const float2*>(bias + nc);
+  f32x4 acc[2][2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) acc[k][0] = acc[k][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      acc[k][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e], w[k][e], acc[k][e & 1], 0, 0, 0);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int mr = t0 + 4 * g4 + r;
+    if (mr < g.Nv)
+      *reinterpret_cast<float2*>(ob + size_t(mr) * g.d + nc) =
+          make_float2(((acc[0][0][r] + acc[0][1][r]) + bv.x) + pv[r].x, ((acc[1][0][r] + acc[1][1][r]) + bv.y) + pv[r].y);
+  }
+}
+
+// what both kernels take of the geometry, and how many floats of the latent are read at once:
+// its rows are multiples of the patch long, so a patch's row starts at a multiple of 4 * p
+// bytes from the base; a base that is aligned to less is read an element at a time
+PatchGeo patch_geo(const Geo& g, int lp) {
+  PatchGeo pg{};
+  pg.T = g.T; pg.Hl = g.Hl; pg.Wl = g.Wl; pg.p = g.p; pg.lp = lp; pg.Hp = g.Hp; pg.Wp = g.Wp;
+  pg.Nv = g.Nv; pg.d = g.d;
+  pg.latent = size_t(g.C) * g.T * g.Hl * g.Wl;
+  pg.h_stride = size_t(g.N) * g.d;
+  pg.txt4 = size_t(g.Nt) * g.d / 4;
+  return pg;
+}
+int vector_width(const Geo& g, const float* x) {
+  const uintptr_t base = reinterpret_cast<uintptr_t>(x);
+  return g.p >= 4 && base % 16 == 0 ? 4 : g.p >= 2 && base % 8 == 0 ? 2 : 1;
+}
+
 }  // namespace
+
+Status patch_embed_f32(const float* x, const float* W, const float* bias, const float* pos, const float* txt,
+                       float* out, const IdxList& idx, const Geo& g, hipStream_t s) {
+  if (idx.n <= 0) return Status::ok();
+  int lp = 0;
+  while ((1 << lp) < g.p) ++lp;
+  if ((1 << lp) != g.p || g.P != 64 || g.d % 128)
+    return Status::shape("fp32 patch embedding needs 64-entry patches, a power-of-two patch, d % 128 == 0");
+  PatchGeo pg = patch_geo(g, lp);
+  pg.groups = g.d / (kPeWaves * 32);
+  pg.items = (g.Nv + kStrip - 1) / kStrip * pg.groups;
+  const dim3 grid(unsigned(pg.items + (pg.txt4 + kPeWaves * 64 - 1) / (kPeWaves * 64)), unsigned(idx.n));
+  const float4* t4 = reinterpret_cast<const float4*>(txt);
+  switch (vector_width(g, x)) {
+    case 4: hipLaunchKernelGGL(k_patch_embed_f32<4>, grid, dim3(kPeWaves * 64), 0, s, x, W, bias, pos, t4, out, idx, pg); break;
+    case 2: hipLaunchKernelGGL(k_patch_embed_f32<2>, grid, dim3(kPeWaves * 64), 0, s, x, W, bias, pos, t4, out, idx, pg); break;
+    default: hipLaunchKernelGGL(k_patch_embed_f32<1>, grid, dim3(kPeWaves * 64), 0, s, x, W, bias, pos, t4, out, idx, pg);
+  }
+  DC_HIP(hipGetLastError());
+  return Status::ok();
+}
 
 Status patch_embed_bf16(const float* x, const float* W, const float* bias, const uint16_t* pos, const float* txt,
                         float* out, const IdxList& idx, const Geo& g, hipStream_t s) {
@@ -239,9 +335,7 @@ Status patch_embed_bf16(const float* x, const float* W, const float* bias, const
     return Status::arg("bf16 patch embedding needs 16-byte aligned device buffers");
   const int cus = compute_units();
   if (cus <= 0) return Status::make(DC_ERR_HIP, "bf16 patch embedding: no device");
-  PatchGeo pg{g.T, g.Hl, g.Wl, g.p, lp, g.Hp, g.Wp};
-  pg.Nv = g.Nv;
-  pg.d = g.d;
+  PatchGeo pg = patch_geo(g, lp);
   pg.groups = (g.d + kPeWaves * kCols - 1) / (kPeWaves * kCols);
   pg.steps = (g.Nv + kStrip * kPeWaves - 1) / (kStrip * kPeWaves);
   // the longest run with which all workgroups are resident at once: W is read once per run
@@ -249,20 +343,13 @@ Status patch_embed_bf16(const float* x, const float* W, const float* bias, const
   pg.run = int((work + kPePerCu * cus - 1) / (kPePerCu * cus));
   pg.items = pg.groups * ((pg.steps + pg.run - 1) / pg.run);
   pg.per_xcd = (pg.items + 7) / 8;
-  pg.latent = size_t(g.C) * g.T * g.Hl * g.Wl;
-  pg.h_stride = size_t(g.N) * g.d;
-  pg.txt4 = size_t(g.Nt) * g.d / 4;
   const dim3 grid(unsigned(8 * pg.per_xcd + (pg.txt4 + kPeWaves * 64 - 1) / (kPeWaves * 64)), unsigned(idx.n));
   const float4* t4 = reinterpret_cast<const float4*>(txt);
-  // rows of the latent are multiples of the patch long, so a patch's row starts at a multiple
-  // of 4 * p bytes from the base; a base that is aligned to less is read an element at a time
-  const uintptr_t base = reinterpret_cast<uintptr_t>(x);
-  if (g.p >= 4 && base % 16 == 0)
-    hipLaunchKernelGGL(k_patch_embed_bf16<4>, grid, dim3(kPeWaves * 64), 0, s, x, W, bias, pos, t4, out, idx, pg);
-  else if (g.p >= 2 && base % 8 == 0)
-    hipLaunchKernelGGL(k_patch_embed_bf16<2>, grid, dim3(kPeWaves * 64), 0, s, x, W, bias, pos, t4, out, idx, pg);
-  else
-    hipLaunchKernelGGL(k_patch_embed_bf16<1>, grid, dim3(kPeWaves * 64), 0, s, x, W, bias, pos, t4, out, idx, pg);
+  switch (vector_width(g, x)) {
+    case 4: hipLaunchKernelGGL(k_patch_embed_bf16<4>, grid, dim3(kPeWaves * 64), 0, s, x, W, bias, pos, t4, out, idx, pg); break;
+    case 2: hipLaunchKernelGGL(k_patch_embed_bf16<2>, grid, dim3(kPeWaves * 64), 0, s, x, W, bias, pos, t4, out, idx, pg); break;
+    default: hipLaunchKernelGGL(k_patch_embed_bf16<1>, grid, dim3(kPeWaves * 64), 0, s, x, W, bias, pos, t4, out, idx, pg);
+  }
   DC_HIP(hipGetLastError());
   return Status::ok();
 }
