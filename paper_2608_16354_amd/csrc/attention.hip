@@ -239,7 +239,8 @@ k_attn_bf16(const uint16_t* __restrict__ qk,
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
       const float mnew = __uint_as_float(uint32_t(to_bf16(mrow + (first ? mx : fmaxf(mx, 0.f)))) << 16);
       const float up = mnew - mrow;
-      const float alpha = __builtin_amdgcn_exp2f(-up);
+      // (up < 0 only on the first tile, where O and l are zero and 2^-up may overflow)
+      const float alpha = __builtin_amdgcn_exp2f(fminf(-up, 0.f));
       mrow = mnew;
       qaug[0] = short(to_bf16(-mnew));
       lsum *= alpha;
@@ -516,7 +517,8 @@ k_attn16(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, int l
     fail = false;
 
     auto rescale = [&](int qb, float up) {      // m += up; O, l *= 2^-up
-      const float a = __builtin_amdgcn_exp2f(-up);
+      // (up < 0 only on the first tile, where O and l are zero and 2^-up may overflow)
+      const float a = __builtin_amdgcn_exp2f(fminf(-up, 0.f));
       mrow[qb] += up;
 #pragma unroll
       for (int i = 0; i < 4; ++i) { lacc[qb][i] *= a; mneg[qb][i] = -mrow[qb]; }

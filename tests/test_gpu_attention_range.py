@@ -1,0 +1,111 @@
+"""The bf16 attention kernels on rows whose scores lie far from zero, against the oracle.
+
+Shapes for each kernel, with and without a split tail (256 compute units): k_attn_bf16 at one
+key tile, at several and at head_dim 72; k_attn16; k_attn_keys.  The block is reduced to its
+attention (W_o = I, gate1 = 1, gate2 = 0), and biases place the scores (log2 units):
+  low        every score of every row near -740;
+  first low  the first 64 keys near -350, the others near zero.
+2^-m of the first tile's maximum m overflows there."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import dit
+from paper_2608_16354_amd import inputs as I
+from tests.gpu_util import rel_l2, say, t
+from tests.test_gpu_edges import _AttentionOnly, _shape
+
+pytestmark = pytest.mark.gpu
+
+# heads, head_dim, frames x rows x columns of patches, text tokens
+SHAPES = {
+    "hd64-N57": (4, 64, (1, 7, 8), 1),
+    "hd72-N63": (16, 72, (1, 7, 8), 7),
+    "hd64-N300-h30": (30, 64, (1, 16, 18), 12),
+    "hd64-N1155-h30": (30, 64, (5, 11, 21), 0),
+    "hd64-N1700-h30": (30, 64, (5, 16, 21), 20),
+    "hd64-N2500-h30": (30, 64, (6, 16, 26), 4),
+    "hd64-N4360-h30": (30, 64, (9, 22, 22), 4),
+    "hd72-N3000-h16": (16, 72, (7, 20, 21), 60),
+    "hd72-N4200-h16": (16, 72, (10, 20, 21), 0),
+}
+
+
+@pytest.fixture(scope="module")
+def api():
+    from paper_2608_16354_amd import api as A
+    A.L.load()
+    return A
+
+
+class _Placed(_AttentionOnly):
+    """_AttentionOnly whose first dimension of every head is a constant query times a key value that
+    is constant ("low") or carried by channel 0 of the token ("first low")."""
+
+    def __init__(self, W, mode):
+        super().__init__(W, 1.0)
+        self.mode = mode
+
+    def block(self, l, name):
+        a = super().block(l, name)
+        d, hd = self.m.hidden, self.m.head_dim
+        if name == "w_qkv":
+            if self.mode != "low":
+                a[:, 0] = 0.0
+                a[: 2 * d: hd] = 0.0
+                a[d: 2 * d: hd, 0] = 2.0
+        elif name == "b_qkv":
+            a = a.copy()
+            a[:d: hd] = -64.0 if self.mode == "low" else -32.0
+            a[d: 2 * d: hd] = 64.0 if self.mode == "low" else 0.0
+        return a
+
+
+def _case(name, mode, key):
+    heads, hd, lat, n_txt = SHAPES[name]
+    m = _shape(heads * hd, heads, hd, 128, (lat[0], 2 * lat[1], 2 * lat[2]), n_txt, "bf16")
+    W = _Placed(I.Weights(m, 160), mode)
+    h = I.hidden_state(m, (key,))
+    h[: m.n_v] /= 0.16                    # rows of unit scale, video and text alike
+    if mode != "low":
+        h[:, 0] = 0.0
+        h[:64, 0] = 30.0
+    mod = np.zeros((6, m.hidden), np.float32)
+    mod[2] = 1.0                          # gate1; gate2 = 0: no MLP
+    return m, W, h, mod
+
+
+def _want(m, W, h, rows):
+    """The attention of the sampled rows in fp64, with a, q, k and v rounded to bf16 where the
+    device rounds them (q after its log2(e)/sqrt(d_h) scale)."""
+    d = m.hidden
+    z = np.zeros(d)
+    a = I.round_bf16(dit.modulate(h.astype(np.float64), z, z, 1e-6).astype(np.float32)).astype(np.float64)
+    w, b = W.block(0, "w_qkv").astype(np.float64), W.block(0, "b_qkv").astype(np.float64)
+    kv = a @ w[d:].T + b[d:]
+    qs = np.float32(1.4426950408889634 / math.sqrt(m.head_dim))
+    q = I.round_bf16((a[rows] @ w[:d].T + b[:d]).astype(np.float32) * qs).astype(np.float64)
+    k = I.round_bf16(kv[:, :d].astype(np.float32)).astype(np.float64)
+    v = I.round_bf16(kv[:, d:].astype(np.float32)).astype(np.float64)
+    return dit.attention(q * (math.sqrt(m.head_dim) * math.log(2.0)), k, v, m.heads)
+
+
+@pytest.mark.parametrize("mode", ["low", "first low"])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_scores_far_below_zero(api, dev, name, mode):
+    import torch
+    m, W, h, mod = _case(name, mode, 80)
+    dm, ws = api.DeviceModel(W, dev), api.Workspace(m, 1, dev)
+    dh = t(h[None], dev)
+    say("attention range", name, mode, "N =", m.n_tok)
+    api.dc_block_forward(dm, 0, t(mod, dev), dh, [0], ws)
+    torch.cuda.synchronize()
+    got = dh[0].cpu().numpy().astype(np.float64) - h
+    assert np.isfinite(got).all()
+    rng = np.random.default_rng(4)
+    rows = np.unique(np.concatenate([[0, min(127, m.n_tok - 1), m.n_tok - 1], rng.integers(0, m.n_tok, 60)]))
+    err = rel_l2(got[rows], _want(m, W, h, rows))
+    say(name, mode, "rel-L2", err)
+    # P and the output are rounded to bf16: 2^-9 each
+    assert err < 5e-3
