@@ -305,7 +305,7 @@ int vector_width(const Geo& g, const float* x) {
 
 Status patch_embed_f32(const float* x, const float* W, const float* bias, const float* pos, const float* txt,
                        float* out, const IdxList& idx, const Geo& g, hipStream_t s) {
-  if (idx.n <= 0) return Status::ok();
+  if (idx.n <= 0 || g.N <= 0) return Status::ok();
   int lp = 0;
   while ((1 << lp) < g.p) ++lp;
   if ((1 << lp) != g.p || g.P != 64 || g.d % 128)
@@ -326,7 +326,7 @@ Status patch_embed_f32(const float* x, const float* W, const float* bias, const 
 
 Status patch_embed_bf16(const float* x, const float* W, const float* bias, const uint16_t* pos, const float* txt,
                         float* out, const IdxList& idx, const Geo& g, hipStream_t s) {
-  if (idx.n <= 0) return Status::ok();
+  if (idx.n <= 0 || g.N <= 0) return Status::ok();
   if (g.P != 64 || g.d % 128) return Status::shape("bf16 patch embedding needs 64-entry patches, d % 128 == 0");
   int lp = 0;
   while ((1 << lp) < g.p) ++lp;
@@ -340,7 +340,7 @@ Status patch_embed_bf16(const float* x, const float* W, const float* bias, const
   pg.steps = (g.Nv + kStrip * kPeWaves - 1) / (kStrip * kPeWaves);
   // the longest run with which all workgroups are resident at once: W is read once per run
   const int64_t work = int64_t(pg.steps) * pg.groups * idx.n;
-  pg.run = int((work + kPePerCu * cus - 1) / (kPePerCu * cus));
+  pg.run = std::max(1, int((work + kPePerCu * cus - 1) / (kPePerCu * cus)));   // (no video tokens: no steps)
   pg.items = pg.groups * ((pg.steps + pg.run - 1) / pg.run);
   pg.per_xcd = (pg.items + 7) / 8;
   const dim3 grid(unsigned(8 * pg.per_xcd + (pg.txt4 + kPeWaves * 64 - 1) / (kPeWaves * 64)), unsigned(idx.n));

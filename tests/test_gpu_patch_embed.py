@@ -58,3 +58,23 @@ def test_patch_embed_edges(dev, d, patch, lat, n_txt, off, dtype):
         # split operands: 2^-17 per product; fp32 sums of 64
         assert err < (1e-5 if dtype == "bf16" else 1e-6)
         assert np.array_equal(got[b, m.n_v:], txt[b])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_txt", [0, 5])
+def test_patch_embed_without_video_tokens(dev, n_txt, dtype):
+    """A latent of no rows: the text rows are all there is, or nothing."""
+    import torch
+    from paper_2608_16354_amd import api
+    m = _shape(256, 2, (1, 0, 8), n_txt, dtype)
+    assert m.n_v == 0 and m.n_tok == n_txt
+    one = _shape(256, 2, (1, 1, 8), n_txt, dtype)       # weights whose pos is not empty
+    dm, ws = api.DeviceModel(_Head(I.Weights(one, 141)), dev), api.Workspace(one, 2, dev)
+    dm.cfg = api.model_cfg(m)
+    txt = I.normal((2, n_txt, 256), 1.0, (142,))
+    h = torch.full((2, n_txt + 1, 256), 7.0, device=dev)
+    say("patch embed without video tokens", dtype, n_txt)
+    api.dc_patch_embed(dm, torch.zeros(64, device=dev), t(txt, dev), h, [0, 1], ws)
+    torch.cuda.synchronize()
+    got = h.cpu().numpy().reshape(-1, 256)
+    assert np.array_equal(got[: 2 * n_txt], txt.reshape(-1, 256)) and (got[2 * n_txt:] == 7.0).all()
