@@ -59,7 +59,7 @@ CalibLayout calib_layout(const Geo& g, int K) {
   auto take = [&](size_t bytes) { const size_t o = off; off = al256(off + bytes); return o; };
   const size_t N = size_t(g.N), Nv = size_t(g.Nv), d = size_t(g.d), F = size_t(g.F);
   const size_t lat = size_t(g.C) * g.T * g.Hl * g.Wl;
-  c.T = std::max(1, std::min(kMaxTangents, 4096 / g.N));
+  c.T = std::max(1, std::min(kMaxTangents, 4096 / std::max(1, g.N)));     // (a model may have no token)
   const size_t R = size_t(c.T + 1) * N;            // rows of a stack: the primal and T tangents
   c.blk_bytes = workspace_layout(g, 1).total;
   c.blk = take(c.blk_bytes);

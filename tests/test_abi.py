@@ -106,6 +106,10 @@ def test_calibration_and_noalloc_entry_points_validate_on_the_host():
     cfg = _lib.ModelCfg(2, 256, 4, 64, 1024, 16, 4, 16, 16, 2, 16, 0, 1e-6)
     assert lib.dc_calibrate_workspace_bytes(C.byref(cfg), 10) > 0
     assert lib.dc_calibrate_workspace_bytes(C.byref(cfg), 0) == 0
+    # a model without tokens (an empty latent, no text) has a size like any other
+    empty = _lib.ModelCfg(2, 256, 4, 64, 1024, 16, 4, 0, 16, 2, 0, 0, 1e-6)
+    assert lib.dc_workspace_bytes(C.byref(empty), 1) > 0
+    assert lib.dc_calibrate_workspace_bytes(C.byref(empty), 10) > 0
     q = (C.c_double * 18)()
     d = (C.c_double * 18)()
     sig = (C.c_double * 11)()
