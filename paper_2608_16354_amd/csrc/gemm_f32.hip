@@ -382,6 +382,7 @@ Status gemm_f32_gate_residual_rows(const float* A, int lda, const void* W, bool 
 
 Status gemm_f32_head_tangents(const float* A, const void* W, bool w_bf16, float* x, float dsigma,
                               const Geo& g, int n, hipStream_t s) {
+  if (g.Nv <= 0) return Status::ok();           // no latent to move (its rows are all text)
   const EpiHeadTangents e{{nullptr, x, dsigma, g.T, g.Hl, g.Wl, g.p, g.Hp, g.Wp}, g.N, g.Nv,
                           size_t(g.C) * g.T * g.Hl * g.Wl};
   if (w_bf16) return gemm(A, g.d, static_cast<const uint16_t*>(W), g.d, n * g.N, g.P, g.d, e, s);

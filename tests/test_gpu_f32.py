@@ -78,6 +78,22 @@ def test_calibration_at_ragged_token_counts(api, dev, lat, n_txt):
     assert np.allclose(q, qo, rtol=1e-5) and np.allclose(d, do, rtol=1e-6)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_calibration_without_video_tokens(api, dev, dtype):
+    """A latent of no rows (text only): nothing to perturb and nothing to measure, every entry 0."""
+    import dataclasses
+    import torch
+    one = dataclasses.replace(_shape(128, (1, 4, 4), 5, n_blocks=1), dtype=dtype)
+    m = dataclasses.replace(one, lat_h=0)
+    assert m.n_v == 0 and m.n_tok == 5
+    dm = api.DeviceModel(I.Weights(one, 124), dev)      # weights whose pos is not empty
+    dm.cfg = api.model_cfg(m)
+    say("calibration without video tokens", dtype)
+    q, d = api.dc_calibrate_tables(dm, torch.zeros(64, device=dev), t(I.normal((5, 128), 1.0, (125,)), dev),
+                                   I.sigmas(4), 2, 1e-6)
+    assert not q.any() and not d.any()
+
+
 def test_time_modulation_many_blocks(api, dev):
     """65 blocks: one more than the offsets one launch of the table takes."""
     import torch
