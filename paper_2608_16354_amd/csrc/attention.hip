@@ -403,10 +403,14 @@ __global__ void __launch_bounds__(256) k_attn_combine(const float* __restrict__ 
 //  - The row sum l is one more MFMA per chunk with an all-ones A operand, so the
 //    VALU does one exp2 and half a bf16 pack per score and nothing else; numerator
 //    and denominator use the same bf16-rounded P.
-//  - m comes from the first tile's maximum and stays there.  When a tile leaves l at
-//    2^64 or more, or not finite (a later score more than about 58 above m), the whole
-//    workgroup redoes the item with the tile maximum taken on every tile (the safe
-//    pass); until then every P is below 2^64, so O cannot overflow.
+//  - m comes from the first tile's maximum.  When a tile leaves l at 2^64 or more (a later
+//    score more than about 58 above m), m is raised after the tile by the exponent of l, if
+//    l and O are finite.  If not (a score more than about 120 above m, or less with huge V),
+//    the wave sits out the rest of the pass and the workgroup redoes the item with the tile
+//    maximum taken on every tile (the safe pass).  us, one key 80 to 97 above the others,
+//    before the raise -> now (as fast as ordinary scores): 2,500 tokens x 30 heads
+//    140 -> 64, 17,776 x 30 4,782 -> 1,969; first tile 290 below the rest, the safe pass:
+//    2,500 x 30 135 -> 119, 17,776 x 30 4,510 -> 3,235.
 // ---------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -499,14 +503,12 @@ k_attn16(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, int l
   for (int e = 0; e < 8; ++e) ones[e] = static_cast<__bf16>(1.0f);
 
   f32x4 o[4][2], lacc[2], mneg[2];
-  float mrow[2];
   bool fail = false;
 
   // one pass over the key tiles; safe: take the tile maximum on every tile
   auto run = [&](bool safe) {
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
-      mrow[qb] = 0.f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) { lacc[qb][i] = 0.f; mneg[qb][i] = 0.f; }
 #pragma unroll
@@ -519,9 +521,9 @@ k_attn16(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, int l
     auto rescale = [&](int qb, float up) {      // m += up; O, l *= 2^-up
       // (up < 0 only on the first tile, where O and l are zero and 2^-up may overflow)
       const float a = __builtin_amdgcn_exp2f(fminf(-up, 0.f));
-      mrow[qb] += up;
+      const float m = up - mneg[qb][0];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { lacc[qb][i] *= a; mneg[qb][i] = -mrow[qb]; }
+      for (int i = 0; i < 4; ++i) { lacc[qb][i] *= a; mneg[qb][i] = -m; }
 #pragma unroll
       for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -603,16 +605,31 @@ k_attn16(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, int l
         }
       }
       body(sk, sv, t, kMask);
-      // m lags the scores by more than about 58 (l >= 2^64, all rows of lacc hold l, or
-      // l not finite): the item is redone in the safe pass.  While l < 2^64, every P
-      // and so O stay far inside the fp32 range.
+      // m lags the scores by more than about 58 (l >= 2^64; all rows of lacc hold l).  While l
+      // and O are finite nothing has overflowed, and m is raised by the exponent of l (at
+      // most 126, so that 2^-up is no denormal); else the item is redone in the safe pass.
       if (!safe) {
         const bool big = !(lacc[0][0] < 0x1p64f && lacc[1][0] < 0x1p64f);
         // a real branch (not a select): it ends the tile's scheduling region, which keeps
-        // the compiler from interleaving tiles (that spills; 144 VGPRs this way)
-        if (__builtin_amdgcn_ballot_w64(big) != 0) {
-          fail = true;
-          __builtin_amdgcn_s_sleep(0);
+        // the compiler from interleaving tiles (that spills), marked unlikely, so that the
+        // registers of the loop are not spilled for it either (14 % slower)
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(big) != 0, 0)) {
+          float z = 0.f;                        // stays 0 if all are finite
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb) {
+            if (!(lacc[qb][0] < 0x1p126f)) z = 1.f;
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) z += o[db][qb][i] * 0.f;
+          }
+          if (__builtin_expect(__builtin_amdgcn_ballot_w64(z != 0.f) != 0, 0)) {
+            fail = true;
+          } else {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+              rescale(qb, lacc[qb][0] < 0x1p64f ? 0.f : float(__builtin_amdgcn_frexp_expf(lacc[qb][0])));
+          }
         }
       }
     };
@@ -635,10 +652,10 @@ k_attn16(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, int l
     else tile(sK0, sV0, tb, kPart, true);
     for (int t = tb + 1; t < tm; t += 2) {
       sync(t, sK0, sV0);
-      tile(sK1, sV1, t, kFull, safe);
+      if (__builtin_expect(!fail, 1)) tile(sK1, sV1, t, kFull, safe);
       if (t + 1 >= tm) break;
       sync(t + 1, sK1, sV1);
-      tile(sK0, sV0, t + 1, kFull, safe);
+      if (__builtin_expect(!fail, 1)) tile(sK0, sV0, t + 1, kFull, safe);
     }
     if (part_last && te - 1 > tb) {
       const int t = te - 1, q = (t - tb) % 2;
@@ -648,7 +665,7 @@ k_attn16(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, int l
   };
 
   // pass 0 is the fast path; pass 1 (rare) redoes the item with the tile maximum on
-  // every tile when any wave saw a non-finite row sum (one call site: one inlined copy)
+  // every tile when any wave gave up (one call site: one inlined copy)
   for (int pass = 0;; ++pass) {
     run(pass > 0);
     if (pass > 0) break;
@@ -668,7 +685,7 @@ k_attn16(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, int l
         *reinterpret_cast<float4*>(rec + 16 * db + 4 * g4) =
             make_float4(o[db][qb][0], o[db][qb][1], o[db][qb][2], o[db][qb][3]);
       if (g4 == 0) {
-        rec[D] = mrow[qb];
+        rec[D] = -mneg[qb][0];
         rec[D + 1] = lacc[qb][0];
       }
     }
@@ -805,6 +822,8 @@ k_attn_keys(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, in
   bool fail = false;
   // l of query block qb: every lane (ones MFMA), or lanes with g4 == (D % 16) / 4
   auto l_of = [&](int qb) { return kOnesRow ? o[DB - 1][qb][0] : lacc[kOnesRow ? 0 : qb][0]; };
+  // the same in every lane
+  auto l_all = [&](int qb) { return kOnesRow ? __shfl(l_of(qb), 16 * ((D % 16) / 4) + c16, 64) : l_of(qb); };
 
   // one pass over the key tiles; safe: take the tile maximum on every tile
   auto run = [&](bool safe) {
@@ -923,17 +942,31 @@ k_attn_keys(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, in
         }
       }
       body(sk, sv, t, kMask);
-      // m lags the scores by more than about 58 (l >= 2^64, or l not finite): the item is
-      // redone in the safe pass.  While l < 2^64, every P and so O stay far inside the fp32
-      // range.
+      // m lags the scores by more than about 58 (l >= 2^64): raised or redone, as in k_attn16
       if (!safe) {
         bool big = !(l_of(0) < 0x1p64f && l_of(1) < 0x1p64f);
         if constexpr (kOnesRow) big = big && g4 == (D % 16) / 4;
         // a real branch (not a select): it ends the tile's scheduling region, which keeps
         // the compiler from interleaving tiles (that spills)
-        if (__builtin_amdgcn_ballot_w64(big) != 0) {
-          fail = true;
-          __builtin_amdgcn_s_sleep(0);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(big) != 0, 0)) {
+          float z = 0.f;                        // stays 0 if all are finite
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb) {
+            if (!(l_of(qb) < 0x1p126f)) z = 1.f;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) z += o[db][qb][i] * 0.f;
+          }
+          if (__builtin_expect(__builtin_amdgcn_ballot_w64(z != 0.f) != 0, 0)) {
+            fail = true;
+          } else {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+              const float l = l_all(qb);
+              rescale(qb, l < 0x1p64f ? 0.f : float(__builtin_amdgcn_frexp_expf(l)));
+            }
+          }
         }
       }
     };
@@ -961,10 +994,10 @@ k_attn_keys(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, in
     else if (ks < te) tile(s0 + off, ks, kPart, true, true);
     for (int i = 1; i < nfl; i += 2) {
       sync(i * KS, s0);
-      tile(s1 + off, i * KS + ks, kFull, safe, false);
+      if (__builtin_expect(!fail, 1)) tile(s1 + off, i * KS + ks, kFull, safe, false);
       if (i + 1 >= nfl) break;
       sync((i + 1) * KS, s1);
-      tile(s0 + off, (i + 1) * KS + ks, kFull, safe, false);
+      if (__builtin_expect(!fail, 1)) tile(s0 + off, (i + 1) * KS + ks, kFull, safe, false);
     }
     if (ragged && nst > 1) {
       const int i = nst - 1, t = i * KS + ks;
@@ -974,7 +1007,7 @@ k_attn_keys(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, in
   };
 
   // pass 0 is the fast path; pass 1 (rare) redoes the item with the tile maximum on
-  // every tile when any wave saw a non-finite row sum (one call site: one inlined copy)
+  // every tile when any wave gave up (one call site: one inlined copy)
   if constexpr (kOnesRow) __syncthreads();      // the ones rows are written
   for (int pass = 0;; ++pass) {
     run(pass > 0);
@@ -985,10 +1018,9 @@ k_attn_keys(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, in
     __syncthreads();
   }
 
-  // l in every lane
   float l[2];
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) l[qb] = kOnesRow ? __shfl(l_of(qb), 16 * ((D % 16) / 4) + c16, 64) : l_of(qb);
+  for (int qb = 0; qb < 2; ++qb) l[qb] = l_all(qb);
 
   // group 1 leaves O, m and l in LDS (the tiles are done with), group 0 merges
   constexpr int ROW = D + 4;
