@@ -252,6 +252,7 @@ __global__ void k_copy4(const float4* __restrict__ src, float4* __restrict__ dst
 struct Sigmas { double v[kModSteps]; };
 constexpr int kModBlocks = 64;
 struct Offsets { const float* p[kModBlocks]; };
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any element
 
 // e[k] = [cos(t w_i), sin(t w_i)], t = 1000 sigma_k, w_i = 10000^(-i/half); in double.
 __global__ void k_time_features(Sigmas sig, float* __restrict__ e, int n_freq) {
@@ -269,23 +270,25 @@ __global__ void k_time_features(Sigmas sig, float* __restrict__ e, int n_freq) {
 // mod[k0 + k, L] = (head_mod + c[k] in rows 0, 1; zeros).  A thread keeps four elements of m[k]
 // and writes them for every block, so the table (71 MB for 50 steps x 30 blocks of 1,920) is
 // one pass of 16-byte stores and one launch: 31 launches of one block each took 106 us.
+// The offsets and mod may start at any element (the 16-byte accesses ask for 4-byte alignment).
 __global__ void __launch_bounds__(256) k_assemble(const float4* __restrict__ m, const float4* __restrict__ c,
-                                                  Offsets off, const float4* __restrict__ head_mod,
+                                                  Offsets off, const f32x4u* __restrict__ head_mod,
                                                   int nl, int l0, int L, int d4, int head,
-                                                  float4* __restrict__ mod) {
+                                                  f32x4u* __restrict__ mod) {
   const int k = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;
   if (e >= 6 * d4) return;
-  float4* dst = mod + size_t(k) * (L + 1) * 6 * d4 + e;
+  f32x4u* dst = mod + size_t(k) * (L + 1) * 6 * d4 + e;
   const float4 v = m[size_t(k) * 6 * d4 + e];
   for (int l = 0; l < nl; ++l) {
-    const float4 o = reinterpret_cast<const float4*>(off.p[l])[e];
-    dst[size_t(l0 + l) * 6 * d4] = make_float4(v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w);
+    const f32x4u o = reinterpret_cast<const f32x4u*>(off.p[l])[e];
+    dst[size_t(l0 + l) * 6 * d4] = f32x4u{v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w};
   }
   if (head) {
-    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+    f32x4u r = {0.f, 0.f, 0.f, 0.f};
     if (e < 2 * d4) {
-      const float4 o = head_mod[e], q = c[size_t(k) * d4 + (e < d4 ? e : e - d4)];
-      r = make_float4(o.x + q.x, o.y + q.y, o.z + q.z, o.w + q.w);
+      const f32x4u o = head_mod[e];
+      const float4 q = c[size_t(k) * d4 + (e < d4 ? e : e - d4)];
+      r = f32x4u{o.x + q.x, o.y + q.y, o.z + q.z, o.w + q.w};
     }
     dst[size_t(L) * 6 * d4] = r;
   }
@@ -400,8 +403,8 @@ Status assemble_modulation(const float* m, const float* c, const float* const* o
     for (int l = 0; l < nl; ++l) off.p[l] = offsets[l0 + l];
     hipLaunchKernelGGL(k_assemble, dim3((6 * d4 + 255) / 256, K), dim3(256), 0, s,
                        reinterpret_cast<const float4*>(m), reinterpret_cast<const float4*>(c), off,
-                       reinterpret_cast<const float4*>(head_mod), nl, l0, g.L, d4, l0 + nl == g.L ? 1 : 0,
-                       reinterpret_cast<float4*>(mod));
+                       reinterpret_cast<const f32x4u*>(head_mod), nl, l0, g.L, d4, l0 + nl == g.L ? 1 : 0,
+                       reinterpret_cast<f32x4u*>(mod));
     DC_LAUNCH_CHECK();
   }
   return Status::ok();

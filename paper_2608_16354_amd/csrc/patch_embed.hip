@@ -36,6 +36,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));   // two floats at any element
 
 constexpr int kStrip = 16;          // tokens per strip
 constexpr int kCols = 64;           // columns per wave
@@ -262,11 +263,11 @@ k_patch_embed_f32(const float* __restrict__ x, const float* __restrict__ W, cons
   for (int k = 0; k < 2; ++k)
 #pragma unroll
     for (int e = 0; e < 16; e += 4) load_v<4>(W + size_t(nc + k) * 64 + 16 * g4 + e, &w[k][e]);
-  float2 pv[4];
+  f32x2u pv[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r)
-    pv[r] = *reinterpret_cast<const float2*>(pos + size_t(min(t0 + 4 * g4 + r, g.Nv - 1)) * g.d + nc);
-  const float2 bv = *reinterpret_cast<const float2*>(bias + nc);
+    pv[r] = *reinterpret_cast<const f32x2u*>(pos + size_t(min(t0 + 4 * g4 + r, g.Nv - 1)) * g.d + nc);
+  const f32x2u bv = *reinterpret_cast<const f32x2u*>(bias + nc);
   f32x4 acc[2][2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) acc[k][0] = acc[k][1] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -279,8 +280,8 @@ k_patch_embed_f32(const float* __restrict__ x, const float* __restrict__ W, cons
   for (int r = 0; r < 4; ++r) {
     const int mr = t0 + 4 * g4 + r;
     if (mr < g.Nv)
-      *reinterpret_cast<float2*>(ob + size_t(mr) * g.d + nc) =
-          make_float2(((acc[0][0][r] + acc[0][1][r]) + bv.x) + pv[r].x, ((acc[1][0][r] + acc[1][1][r]) + bv.y) + pv[r].y);
+      *reinterpret_cast<f32x2u*>(ob + size_t(mr) * g.d + nc) =
+          f32x2u{((acc[0][0][r] + acc[0][1][r]) + bv.x) + pv[r].x, ((acc[1][0][r] + acc[1][1][r]) + bv.y) + pv[r].y};
   }
 }
 

@@ -131,3 +131,38 @@ def test_time_modulation_tiles(api, dev, d, K):
         assert rel_l2(got[k, 0], blocks[0]) < 1e-5
         assert rel_l2(got[k, 1, :2], head) < 1e-5
         assert not got[k, 1, 2:].any()
+
+
+def _one_off(a, dev):
+    """a copied to a base one element past an aligned one."""
+    import torch
+    room = torch.zeros(a.numel() + 1, device=dev)
+    room[1:].copy_(a.reshape(-1))
+    return room[1:].view(a.shape)
+
+
+def test_buffers_at_any_element(api, dev):
+    """Position table, bias and output of the fp32 patch embedding, and the offsets and table of the
+    modulation, whose bases are aligned to 4 bytes only: the results of aligned buffers, bit for bit."""
+    import torch
+    m = _shape(256, (2, 6, 10), 0, n_blocks=2)
+    dm, ws = api.DeviceModel(I.Weights(m, 126), dev), api.Workspace(m, 1, dev)
+    x, sig = t(I.latent(m, 126, 0)[None], dev), np.array([0.7, 0.2, 0.1])
+
+    def run(h, mod):
+        say("buffers", "aligned to", int(h.data_ptr()) & -int(h.data_ptr()))
+        api.dc_patch_embed(dm, x, None, h, [0], ws)
+        api.dc_time_modulation(dm, sig, mod, ws)
+        torch.cuda.synchronize()
+        return h.clone(), mod.clone()
+
+    h, mod = torch.zeros((1, m.n_tok, 256), device=dev), torch.zeros((3, m.n_blocks + 1, 6, 256), device=dev)
+    want = run(h, mod)
+    keep = {n: _one_off(dm.g[n], dev) for n in ("pos", "b_pe", "head_mod")}
+    for n, a in keep.items():
+        setattr(dm.cweights, n, a.data_ptr())
+    offsets = [_one_off(b["mod_offset"], dev) for b in dm.blocks]
+    for c, a in zip(dm._cblocks, offsets):
+        c.mod_offset = a.data_ptr()
+    got = run(_one_off(torch.zeros_like(h), dev), _one_off(torch.zeros_like(mod), dev))
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
