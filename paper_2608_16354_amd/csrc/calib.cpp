@@ -44,7 +44,7 @@ namespace {
 inline size_t al256(size_t v) { return (v + 255) & ~size_t(255); }
 
 struct CalibLayout {
-  size_t blk, blk_bytes, mod, xs, us, rs, h_in, h, a, qkv, o, z, patches, zeros, v, dx, G, red, norms, total;
+  size_t blk, blk_bytes, mod, xs, us, rs, h_in, h, a, qkv, o, z, patches, v, dx, G, red, norms, total;
   int T;                 // tangents per group
 };
 
@@ -74,7 +74,6 @@ CalibLayout calib_layout(const Geo& g, int K) {
   c.o = take(R * d * 4);
   c.z = take(R * F * 4);
   c.patches = take(size_t(c.T) * N * 64 * 4);
-  c.zeros = take(d * 4);
   c.v = take(size_t(c.T + 1) * lat * 4);
   c.dx = take(size_t(c.T) * lat * 4);
   c.G = take(size_t(K) * lat * 4);
@@ -172,8 +171,8 @@ struct Calib {
     const int d = g.d, N = g.N;
     DC_TRY(patch_embed(g, w, x_at(k), txt, F(L.h), one, blk(), L.blk_bytes, s));
     DC_TRY(patchify_tangents(F(L.dx), F(L.patches), g, n, s));            // text rows carry no tangent
-    DC_TRY(gemm_f32_rows(F(L.patches), 64, w->w_pe, false, 64, F(L.zeros), 0, F(L.h) + size_t(N) * d, d, n * N, d,
-                         64, s));
+    DC_TRY(gemm_f32_rows(F(L.patches), 64, w->w_pe, false, 64, w->b_pe, 0, F(L.h) + size_t(N) * d, d, n * N, d, 64,
+                         s));                                             // (no row gets the bias)
     for (int l = 0; l < g.L; ++l) DC_TRY(block_jvp(l, mk + size_t(l) * 6 * d, n));
     const float* hm = mk + size_t(g.L) * 6 * d;
     DC_TRY(ln_mod_jvp(F(L.h), n, N, d, hm, hm + d, F(L.a), g.eps, s));
@@ -203,7 +202,6 @@ Status calibrate_tables(const Geo& g, const dc_model_weights* w, const float* x1
   Calib c{g, w, txt, sigmas, K, ws, L, s, {}, size_t(g.C) * g.T * g.Hl * g.Wl, size_t(g.L + 1) * 6 * g.d};
   const int32_t zero = 0;
   DC_TRY(make_idx(&zero, 1, c.one));
-  DC_HIP(hipMemsetAsync(c.F(L.zeros), 0, size_t(g.d) * 4, s));
   DC_HIP(hipMemsetAsync(c.F(L.G), 0, size_t(K) * c.lat * 4, s));
   DC_TRY(time_modulation(g, w, sigmas, K, c.F(L.mod), c.blk(), L.blk_bytes, s));
   DC_TRY(c.trace(x1));
