@@ -739,7 +739,7 @@ k_attn_keys(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, in
 
   const int w = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (w >= items) return;
-  const int te = (M + BKV - 1) / BKV;           // key tiles
+  const int te = (M + BKV - 1) / BKV;           // key tiles, at least one per group (M > 64)
   const int head = w / nqb;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -991,7 +991,7 @@ k_attn_keys(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, in
     issue(s0, 0);
     sync(0, s1);
     if (nfl > 0) tile(s0 + off, ks, kFull, true, true);
-    else if (ks < te) tile(s0 + off, ks, kPart, true, true);
+    else tile(s0 + off, ks, kPart, true, true);
     for (int i = 1; i < nfl; i += 2) {
       sync(i * KS, s0);
       if (__builtin_expect(!fail, 1)) tile(s1 + off, i * KS + ks, kFull, safe, false);
@@ -1044,23 +1044,21 @@ k_attn_keys(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt, in
   }
   __syncthreads();
   if (ks > 0) return;
-  if (te > 1) {                                  // group 1 had a tile
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      const float* rec = mem + (qw * 32 + 16 * qb + c16) * ROW;
-      const float m1 = rec[D], m = fmaxf(mrow[qb], m1);
-      const float a0 = __builtin_amdgcn_exp2f(mrow[qb] - m), a1 = __builtin_amdgcn_exp2f(m1 - m);
-      l[qb] = l[qb] * a0 + rec[D + 1] * a1;
+  for (int qb = 0; qb < 2; ++qb) {
+    const float* rec = mem + (qw * 32 + 16 * qb + c16) * ROW;
+    const float m1 = rec[D], m = fmaxf(mrow[qb], m1);
+    const float a0 = __builtin_amdgcn_exp2f(mrow[qb] - m), a1 = __builtin_amdgcn_exp2f(m1 - m);
+    l[qb] = l[qb] * a0 + rec[D + 1] * a1;
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
-        if (16 * db + 4 * g4 < D) {
-          const float4 x = *reinterpret_cast<const float4*>(rec + 16 * db + 4 * g4);
-          o[db][qb][0] = o[db][qb][0] * a0 + x.x * a1;
-          o[db][qb][1] = o[db][qb][1] * a0 + x.y * a1;
-          o[db][qb][2] = o[db][qb][2] * a0 + x.z * a1;
-          o[db][qb][3] = o[db][qb][3] * a0 + x.w * a1;
-        }
-    }
+    for (int db = 0; db < DB; ++db)
+      if (16 * db + 4 * g4 < D) {
+        const float4 x = *reinterpret_cast<const float4*>(rec + 16 * db + 4 * g4);
+        o[db][qb][0] = o[db][qb][0] * a0 + x.x * a1;
+        o[db][qb][1] = o[db][qb][1] * a0 + x.y * a1;
+        o[db][qb][2] = o[db][qb][2] * a0 + x.z * a1;
+        o[db][qb][3] = o[db][qb][3] * a0 + x.w * a1;
+      }
   }
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {

@@ -339,7 +339,8 @@ Status patch_embed_bf16(const float* x, const float* W, const float* bias, const
   PatchGeo pg = patch_geo(g, lp);
   pg.groups = (g.d + kPeWaves * kCols - 1) / (kPeWaves * kCols);
   pg.steps = (g.Nv + kStrip * kPeWaves - 1) / (kStrip * kPeWaves);
-  // the longest run with which all workgroups are resident at once: W is read once per run
+  // about as many workgroups as are resident at once, since W is read once per run (runs that do
+  // not divide a sample's steps, and the text rows, can make it a few more)
   const int64_t work = int64_t(pg.steps) * pg.groups * idx.n;
   pg.run = std::max(1, int((work + kPePerCu * cus - 1) / (kPePerCu * cus)));   // (no video tokens: no steps)
   pg.items = pg.groups * ((pg.steps + pg.run - 1) / pg.run);
