@@ -89,9 +89,7 @@ Workspace workspace_layout(const Geo& g, int batch) {
   w.ff = take(size_t(g.N) * g.F * g.esz);
   (void)batch;
   w.drift_part = take(size_t(DC_MAX_BATCH) * kDriftBlocks * 4 * sizeof(double));
-  // split-tail partials of the bf16 attention: up to 64 split items per XCD, two halves of
-  // 128 queries x (head_dim + 4) floats each
-  w.attn_part_bytes = g.bf16 ? size_t(8) * 64 * 2 * 128 * (g.Dh + 4) * sizeof(float) : 0;
+  w.attn_part_bytes = g.bf16 ? attn_part_bytes(g.Dh) : 0;
   w.attn_part = take(w.attn_part_bytes);
   w.tm_e = take(size_t(kModSteps) * 256 * 4);
   w.tm_h = take(size_t(kModSteps) * g.d * 4);

@@ -1112,18 +1112,21 @@ static int attn16_slots_per_xcd() {
   return cache[dev];
 }
 
+// How many of an XCD's items run whole (launch_attn): the items of the last partial round are
+// split when their halves fit in one round.
+static int whole_items(int per_xcd, int slots, int M, int D, size_t part_bytes) {
+  if (slots <= 0 || (M + 63) / 64 < 2) return per_xcd;
+  const int f = per_xcd / slots * slots, r = per_xcd - f;
+  const size_t need = size_t(8) * r * 2 * 128 * (D + 4) * sizeof(float);
+  return r > 0 && 2 * r <= slots && need <= part_bytes ? f : per_xcd;
+}
+
 template <int D, bool V16>
 static Status launch_attn(const uint16_t* qk, const uint16_t* vt, int ldv, uint16_t* out, const Geo& g,
                           int M, float* part, size_t part_bytes, hipStream_t s) {
   const int nqb = (M + 127) / 128, items = nqb * g.H, per_xcd = (items + 7) / 8;
-  // split the items of the last partial round when their halves fit in one round
   const int slots = V16 ? attn16_slots_per_xcd() : attn_slots_per_xcd<D>();
-  int full = per_xcd;
-  if (slots > 0 && (M + 63) / 64 >= 2) {
-    const int f = per_xcd / slots * slots, r = per_xcd - f;
-    const size_t need = size_t(8) * r * 2 * 128 * (D + 4) * sizeof(float);
-    if (r > 0 && 2 * r <= slots && part && need <= part_bytes) full = f;
-  }
+  const int full = whole_items(per_xcd, slots, M, D, part ? part_bytes : 0);
   const int units = full + 2 * (per_xcd - full);
   if constexpr (V16)
     hipLaunchKernelGGL(k_attn16, dim3(8 * units), dim3(256), 0, s, qk, vt, ldv, out, M, g.d, nqb, items,
@@ -1150,26 +1153,44 @@ static Status launch_keys(const uint16_t* qk, const uint16_t* vt, int ldv, uint1
   return Status::ok();
 }
 
+// Which kernel (256 compute units, us, head_dim 64 unless noted):
+//  - k_attn_keys while its items (64 queries of a head) are at most two per compute unit, from two
+//    key tiles on: 300 tokens x 30 heads 6.8, k_attn_bf16 12.2; 1,556 x 20 (500 items) 18.9 and
+//    34.5; head_dim 72, 2,000 x 16 (512) 29.2 and 38.2, 3,000 x 16 (752) 64.7 and 57.7;
+//  - k_attn16 (head_dim 64) from 2.25 items of 128 queries per compute unit: 5,000 x 48 (1,920
+//    items) 276, k_attn_bf16 304; 2,500 x 30 (600) 56.9 and 57.7; 5,000 x 12 (480) 87 and 80.5;
+//    17,776 x 30 1,916 and 2,127;
+//  - k_attn_bf16 between, and for head_dim 72.
+AttnKernel attention_kernel(int head_dim, int heads, int tokens, int cus) {
+  if (tokens > 64 && int64_t(heads) * ((tokens + 63) / 64) <= 2 * int64_t(cus)) return AttnKernel::kKeys;
+  if (head_dim == 64 && 4 * int64_t(heads) * ((tokens + 127) / 128) >= 9 * int64_t(cus)) return AttnKernel::k16;
+  return AttnKernel::kBf16;
+}
+
+bool attention_splits(int head_dim, int heads, int tokens) {
+  const AttnKernel k = attention_kernel(head_dim, heads, tokens, compute_units());
+  if (k == AttnKernel::kKeys) return false;
+  const int slots = k == AttnKernel::k16 ? attn16_slots_per_xcd()
+                    : head_dim == 64     ? attn_slots_per_xcd<64>()
+                                         : attn_slots_per_xcd<72>();
+  const int per_xcd = (heads * ((tokens + 127) / 128) + 7) / 8;
+  return whole_items(per_xcd, slots, tokens, head_dim, attn_part_bytes(head_dim)) < per_xcd;
+}
+
 Status attention_bf16(const uint16_t* qk, const uint16_t* vt, int ldv, uint16_t* out,
                       const Geo& g, int M, float* part, size_t part_bytes, hipStream_t s) {
   if (ldv % 64 || ldv < M) return Status::shape("attention needs ldv >= M, ldv % 64 == 0");
   // the padding tokens [M, ldv) of vt hold zeros: the bf16 QKV GEMM writes them
   if (g.Dh != 64 && g.Dh != 72) return Status::shape("bf16 attention supports head_dim 64 and 72");
-  const int64_t cus = compute_units();
+  const int cus = compute_units();
   if (cus <= 0) return Status::make(DC_ERR_HIP, "bf16 attention: no device");
-  // Which kernel (256 compute units, us, head_dim 64 unless noted):
-  //  - k_attn_keys while its items (64 queries of a head) are at most two per compute unit, from two
-  //    key tiles on: 300 tokens x 30 heads 6.8, k_attn_bf16 12.2; 1,556 x 20 (500 items) 18.9 and
-  //    34.5; head_dim 72, 2,000 x 16 (512) 29.2 and 38.2, 3,000 x 16 (752) 64.7 and 57.7;
-  //  - k_attn16 (head_dim 64) from 2.25 items of 128 queries per compute unit: 5,000 x 48 (1,920
-  //    items) 276, k_attn_bf16 304; 2,500 x 30 (600) 56.9 and 57.7; 5,000 x 12 (480) 87 and 80.5;
-  //    17,776 x 30 1,916 and 2,127;
-  //  - k_attn_bf16 between, and for head_dim 72.
-  if (M > 64 && int64_t(g.H) * ((M + 63) / 64) <= 2 * cus)
-    return g.Dh == 64 ? launch_keys<64>(qk, vt, ldv, out, g, M, s) : launch_keys<72>(qk, vt, ldv, out, g, M, s);
+  switch (attention_kernel(g.Dh, g.H, M, cus)) {
+    case AttnKernel::kKeys:
+      return g.Dh == 64 ? launch_keys<64>(qk, vt, ldv, out, g, M, s) : launch_keys<72>(qk, vt, ldv, out, g, M, s);
+    case AttnKernel::k16: return launch_attn<64, true>(qk, vt, ldv, out, g, M, part, part_bytes, s);
+    default: break;
+  }
   if (g.Dh == 72) return launch_attn<72, false>(qk, vt, ldv, out, g, M, part, part_bytes, s);
-  if (4 * int64_t(g.H) * ((M + 127) / 128) >= 9 * cus)
-    return launch_attn<64, true>(qk, vt, ldv, out, g, M, part, part_bytes, s);
   return launch_attn<64, false>(qk, vt, ldv, out, g, M, part, part_bytes, s);
 }
 

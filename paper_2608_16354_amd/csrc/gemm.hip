@@ -558,7 +558,9 @@ constexpr TileCost kTiles[] = {{384, 192, 1.168f, 1.706f, 11.2f}, {320, 256, 1.2
                                {128, 128, 0.341f, 0.471f, 3.9f},  {64, 64, 0.f, 0.f, 2.1f}};
 constexpr float kSmallStep[3] = {0.302f, 0.401f, 0.496f};
 
-int pick_tile(int M, int N, int K, int cus) {
+}  // namespace
+
+int block_gemm_tile(int M, int N, int K, int cus) {
   const float steps = float(K / 64);
   int best = 0;
   float least = 0.f;
@@ -583,6 +585,8 @@ int pick_tile(int M, int N, int K, int cus) {
   return best;
 }
 
+namespace {
+
 template <class Epi>
 Status block_gemm(const uint16_t* A, int lda, const uint16_t* W, int ldw, int M, int N, int K,
                   const Epi& epi, hipStream_t s) {
@@ -590,7 +594,7 @@ Status block_gemm(const uint16_t* A, int lda, const uint16_t* W, int ldw, int M,
   DC_TRY(check_gemm(lda, ldw, M, N, K));
   const int cus = compute_units();
   if (cus <= 0) return Status::make(DC_ERR_HIP, "bf16 GEMM: no device");
-  switch (pick_tile(M, N, K, cus)) {
+  switch (block_gemm_tile(M, N, K, cus)) {
     case 0: return launch_dma<384, 192, 4, 2, 2, 2>(A, lda, W, ldw, M, N, K, epi, s);
     case 1: return launch_dma<320, 256, 2, 4, 2, 2>(A, lda, W, ldw, M, N, K, epi, s);
     case 2: return launch_dma<256, 192, 4, 2, 2, 2>(A, lda, W, ldw, M, N, K, epi, s);

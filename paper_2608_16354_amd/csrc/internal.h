@@ -99,6 +99,10 @@ struct Workspace {
 };
 Workspace workspace_layout(const Geo& g, int batch);
 
+// split-tail partials of the bf16 attention: up to 64 split items per XCD, two halves of
+// 128 queries x (head_dim + 4) floats each
+inline size_t attn_part_bytes(int head_dim) { return size_t(8) * 64 * 2 * 128 * (head_dim + 4) * sizeof(float); }
+
 constexpr int kModSteps = 64;       // denoising steps per pass of the modulation
 constexpr int kDriftBlocks = 1024;  // fixed grid per sample: reproducible reductions
 
@@ -134,7 +138,8 @@ Status gemm_f32_gate_residual_rows(const float* A, int lda, const void* W, bool 
 Status gemm_f32_head_tangents(const float* A, const void* W, bool w_bf16, float* x, float dsigma,
                               const Geo& g, int n, hipStream_t s);
 
-// bf16 MFMA GEMM variants.
+// bf16 MFMA GEMM variants.  block_gemm_tile: which of its six tiles a call takes (gemm.hip, kTiles).
+int block_gemm_tile(int M, int N, int K, int cus);
 Status gemm_bf16_qkv(const uint16_t* A, const uint16_t* W, const float* bias, uint16_t* qk,
                      uint16_t* vt, int ldv, const Geo& g, int M, hipStream_t s);
 Status gemm_bf16_gate_residual(const uint16_t* A, int lda, const uint16_t* W, const float* bias,
@@ -162,6 +167,11 @@ Status head_euler_bf16(const float* gin, const uint16_t* resid, const uint16_t* 
 // with too little scratch the tail is not split.
 Status attention_bf16(const uint16_t* qk, const uint16_t* vt, int ldv, uint16_t* out,
                       const Geo& g, int M, float* part, size_t part_bytes, hipStream_t s);
+// Which of its kernels that call takes, and whether items of its last round are split (with the
+// scratch of a workspace; false without a device).
+enum class AttnKernel { kKeys, kBf16, k16 };
+AttnKernel attention_kernel(int head_dim, int heads, int tokens, int cus);
+bool attention_splits(int head_dim, int heads, int tokens);
 // fp32 attention over qkv [M, 3d] (Q | K | V), out [M, d] (attention_f32.hip).
 Status attention_f32(const float* qkv, float* out, const Geo& g, int M, hipStream_t s);
 

@@ -1,8 +1,11 @@
-"""The bf16 attention kernels on rows whose scores lie far from zero, against the oracle.
+"""The bf16 attention kernels over their dispatch, on rows whose scores lie near zero and far from
+it, against the oracle.
 
-Shapes for each kernel, with and without a split tail (256 compute units): k_attn_bf16 at one
-key tile, at several and at head_dim 72; k_attn16; k_attn_keys.  The block is reduced to its
-attention (W_o = I, gate1 = 1, gate2 = 0), and biases place the scores (log2 units):
+Shapes for each kernel, ragged, with and without a split tail; each names the kernel it takes on
+256 compute units and whether items are split (asserted against attention_kernel and
+attention_splits in attention.hip).  The block is reduced to its attention (W_o = I, gate1 = 1,
+gate2 = 0), and biases place the scores (log2 units):
+  plain      all near zero;
   low        every score of every row near -740;
   first low  the first 64 keys near -350, the others near zero;
   rise       some keys of later tiles about 90 above the others;
@@ -16,23 +19,23 @@ import pytest
 
 from oracle import dit
 from paper_2608_16354_amd import inputs as I
-from tests.gpu_util import rel_l2, say, t
+from tests.gpu_util import attention_kernel, attention_splits, compute_units, rel_l2, say, t
 from tests.test_gpu_edges import _AttentionOnly, _shape
 
 pytestmark = pytest.mark.gpu
 
-# heads, head_dim, frames x rows x columns of patches, text tokens
+# heads, head_dim, frames x rows x columns of patches, text tokens; kernel, split
 SHAPES = {
-    "hd64-N57": (4, 64, (1, 7, 8), 1),
-    "hd72-N63": (16, 72, (1, 7, 8), 7),
-    "hd64-N300-h30": (30, 64, (1, 16, 18), 12),
-    "hd64-N1155-h30": (30, 64, (5, 11, 21), 0),
-    "hd64-N1700-h30": (30, 64, (5, 16, 21), 20),
-    "hd64-N2500-h30": (30, 64, (6, 16, 26), 4),
-    "hd64-N4360-h30": (30, 64, (9, 22, 22), 4),
-    "hd72-N2000-h16": (16, 72, (5, 20, 20), 0),
-    "hd72-N3000-h16": (16, 72, (7, 20, 21), 60),
-    "hd72-N4200-h16": (16, 72, (10, 20, 21), 0),
+    "hd64-N57": (4, 64, (1, 7, 8), 1, "k_attn_bf16", False),
+    "hd72-N63": (16, 72, (1, 7, 8), 7, "k_attn_bf16", False),
+    "hd64-N300-h30": (30, 64, (1, 16, 18), 12, "k_attn_keys", False),
+    "hd72-N2000-h16": (16, 72, (5, 20, 20), 0, "k_attn_keys", False),
+    "hd64-N1155-h30": (30, 64, (5, 11, 21), 0, "k_attn_bf16", True),      # 38 items per XCD, all split
+    "hd64-N1700-h30": (30, 64, (5, 16, 21), 20, "k_attn_bf16", False),    # 53 of 96 slots
+    "hd72-N3000-h16": (16, 72, (7, 20, 21), 60, "k_attn_bf16", False),    # 48 of 64 slots
+    "hd72-N4200-h16": (16, 72, (10, 20, 21), 0, "k_attn_bf16", True),     # 66 items on 64 slots
+    "hd64-N2500-h30": (30, 64, (6, 16, 26), 4, "k_attn16", False),        # 75 of 128 slots
+    "hd64-N4360-h30": (30, 64, (9, 22, 22), 4, "k_attn16", True),         # 132 items on 128 slots
 }
 
 
@@ -63,16 +66,20 @@ class _Placed(_AttentionOnly):
                 a[2 * d:] *= np.float32(2.0 ** 50)
         elif name == "b_qkv":
             a = a.copy()
-            a[:d: hd] = {"low": -64.0, "first low": -32.0}.get(self.mode, 8.0)
+            a[:d: hd] = {"plain": 0.0, "low": -64.0, "first low": -32.0}.get(self.mode, 8.0)
             a[d: 2 * d: hd] = 64.0 if self.mode == "low" else 0.0
             if self.mode == "rise, v":
                 a[2 * d:] *= np.float32(2.0 ** 50)
         return a
 
 
+def model(name):
+    heads, hd, lat, n_txt = SHAPES[name][:4]
+    return _shape(heads * hd, heads, hd, 128, (lat[0], 2 * lat[1], 2 * lat[2]), n_txt, "bf16")
+
+
 def _case(name, mode, key):
-    heads, hd, lat, n_txt = SHAPES[name]
-    m = _shape(heads * hd, heads, hd, 128, (lat[0], 2 * lat[1], 2 * lat[2]), n_txt, "bf16")
+    m = model(name)
     W = _Placed(I.Weights(m, 160), mode)
     h = I.hidden_state(m, (key,))
     h[: m.n_v] /= 0.16                    # rows of unit scale, video and text alike
@@ -80,7 +87,7 @@ def _case(name, mode, key):
         h[:, 0] = 0.0
         if mode == "first low":
             h[:64, 0] = 30.0
-        else:
+        elif mode != "plain":
             h[70::97, 0] = 30.0
             h[-1, 0] = 30.0
     mod = np.zeros((6, m.hidden), np.float32)
@@ -103,10 +110,12 @@ def _want(m, W, h, rows):
     return dit.attention(q * (math.sqrt(m.head_dim) * math.log(2.0)), k, v, m.heads)
 
 
-@pytest.mark.parametrize("mode", ["low", "first low", "rise", "rise, v"])
+@pytest.mark.parametrize("mode", ["plain", "low", "first low", "rise", "rise, v"])
 @pytest.mark.parametrize("name", list(SHAPES))
-def test_scores_far_from_zero(api, dev, name, mode):
+def test_scores_at_any_place(api, dev, name, mode):
     import torch
+    kernel, split = SHAPES[name][4:]
+    assert (attention_kernel(model(name), compute_units(dev)), attention_splits(model(name))) == (kernel, split)
     m, W, h, mod = _case(name, mode, 80)
     dm, ws = api.DeviceModel(W, dev), api.Workspace(m, 1, dev)
     dh = t(h[None], dev)

@@ -2,11 +2,11 @@
 
 Small seeded models whose token counts leave ragged tails everywhere: fewer
 tokens than one attention tile (37, head_dim 72), fewer than one MFMA row tile
-and no text (16), one partial GEMM row tile (111), several row tiles, attention
-tiles and query blocks with a ragged last one (328), the fp32 path at a
-ragged count (95), and 3,597 tokens x 30 heads, where the attention's query
-blocks outnumber the resident workgroups by just over three rounds on MI355X, so
-the last partial round runs as split key halves merged by the combine kernel.
+and no text (16), one partial GEMM row tile (111), several row tiles and key
+tiles with a ragged last one (328), the fp32 path at a ragged count (95), and
+3,597 tokens x 30 heads, the long-sequence attention kernel below a full round of
+workgroups (the kernels' other shapes, split tails among them:
+test_gpu_attention_range.py).
 The fused head's extremes: one video token (one partial token tile) at d = 256
 (one 32-wide chunk per wave) and d = 2048 (eight chunks per wave).
 Also: empty index lists leave every buffer untouched."""
@@ -32,7 +32,7 @@ EDGE = {
     "bf16-N111": (_shape(256, 4, 64, 1024, (3, 10, 12), 21, "bf16"), 93),
     "bf16-N328": (_shape(384, 6, 64, 1536, (5, 14, 18), 13, "bf16"), 94),
     "f32-N95": (_shape(256, 4, 64, 1024, (3, 10, 12), 5, "f32"), 95),
-    "bf16-N3597-h30-split": (_shape(1920, 30, 64, 7680, (10, 32, 44), 77, "bf16"), 96),
+    "bf16-N3597-h30": (_shape(1920, 30, 64, 7680, (10, 32, 44), 77, "bf16"), 96),
     "bf16-N1-d256": (_shape(256, 4, 64, 1024, (1, 2, 2), 3, "bf16"), 97),
     "bf16-N40-d2048": (_shape(2048, 32, 64, 8192, (2, 8, 10), 5, "bf16"), 98),
 }
@@ -233,7 +233,7 @@ def test_attention_large_logits(api, dev):
     assert err < 1e-2
 
 
-@pytest.mark.parametrize("name", ["bf16-N328", "bf16-N3597-h30-split"])
+@pytest.mark.parametrize("name", ["bf16-N328", "bf16-N3597-h30"])
 def test_head_rows_with_large_mean_and_outlier_first_value(api, dev, name):
     """The head's LayerNorm on rows whose mean is 40 standard deviations from zero, some
     with a first value 900 standard deviations from the mean: the LN statistics and the
