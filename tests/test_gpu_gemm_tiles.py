@@ -1,14 +1,15 @@
 """The bf16 block GEMMs' tile shapes at ragged sizes, against the oracle.
 
-Each shape makes the tile choice of at least one of the block's GEMMs land on another of the
-six tiles (see pick_tile in gemm.hip): token counts one short of and one past a multiple of
-the tile heights, and widths whose columns leave part of a column tile empty."""
+Each shape names the tiles that its QKV, out-projection, MLP-up and MLP-down GEMM take on 256
+compute units (asserted against block_gemm_tile in gemm.hip), all six of them among the shapes:
+token counts one short of and one past a multiple of the tile heights, and widths whose columns
+leave part of a column tile empty."""
 import numpy as np
 import pytest
 
 from oracle import dit
 from paper_2608_16354_amd import inputs as I
-from tests.gpu_util import mod_input, rel_l2, say, t
+from tests.gpu_util import block_tiles, compute_units, mod_input, rel_l2, say, t
 from tests.test_gpu_kernels import _OneBlock
 
 pytestmark = pytest.mark.gpu
@@ -20,13 +21,14 @@ def _shape(d, heads, hd, f, lat, n_txt):
 
 
 SHAPES = {
-    "d128-N2-k2": _shape(128, 2, 64, 128, (1, 2, 2), 1),             # 64 x 64, two k-steps
-    "d128-N129": _shape(128, 2, 64, 256, (1, 16, 32), 1),
-    "d640-N257": _shape(640, 10, 64, 2560, (1, 32, 32), 1),          # 64 x 64
-    "d1152-N1537-hd72": _shape(1152, 16, 72, 4608, (3, 32, 64), 1),  # 64, 128 and 256 x 128
-    "d1920-N1155": _shape(1920, 30, 64, 7680, (5, 22, 42), 0),       # 128 x 128
-    "d1920-N2562": _shape(1920, 30, 64, 7680, (10, 32, 32), 2),      # 256 x 128, 320 x 256
-    "d3072-N2305": _shape(3072, 48, 64, 12288, (9, 32, 32), 1),      # 256 x 192
+    "d128-N2-k2": (_shape(128, 2, 64, 128, (1, 2, 2), 1), ("64x64",) * 4),             # two k-steps
+    "d128-N129": (_shape(128, 2, 64, 256, (1, 16, 32), 1), ("64x64",) * 4),
+    "d640-N257": (_shape(640, 10, 64, 2560, (1, 32, 32), 1), ("64x64",) * 4),
+    "d1152-N1537-hd72": (_shape(1152, 16, 72, 4608, (3, 32, 64), 1), ("256x128", "64x64", "256x128", "64x64")),
+    "d1920-N1155": (_shape(1920, 30, 64, 7680, (5, 22, 42), 0), ("256x128", "128x128", "256x192", "128x128")),
+    "d1920-N2562": (_shape(1920, 30, 64, 7680, (10, 32, 32), 2), ("384x192", "256x128", "256x192", "128x128")),
+    "d2176-N2879": (_shape(2176, 34, 64, 6528, (8, 34, 42), 23), ("320x256", "256x128", "320x256", "128x128")),
+    "d3072-N2305": (_shape(3072, 48, 64, 12288, (9, 32, 32), 1), ("256x192", "256x128", "384x192", "128x128")),
 }
 
 
@@ -40,7 +42,8 @@ def api():
 @pytest.mark.parametrize("name", list(SHAPES))
 def test_block_at_tile_edges(api, dev, name):
     import torch
-    m = SHAPES[name]
+    m, tiles = SHAPES[name]
+    assert block_tiles(m, compute_units(dev)) == tiles
     W = I.Weights(m, 130)
     dm = api.DeviceModel(_OneBlock(W, 0), dev)
     ws = api.Workspace(m, 1, dev)
