@@ -43,8 +43,35 @@ def test_head_edges(dev, d, patch, lat):
     want = dit.euler(x[1].astype(np.float64), v, 0.52, 0.5)
     err = rel_l2(got[1] - x[1], want - x[1])
     say("head update rel-L2", err)
-    # hi + lo operands keep 2^-17; the update is read back from x at fp32: |x| / |update| x 2^-24
-    assert err < 1e-4
+    # hi + lo operands keep 2^-17 = 7.6e-6; the update is read back from x at fp32: |x| / |update| x
+    # 2^-24, about 50 x 6e-8
+    assert err < 2e-5
+
+
+@pytest.mark.parametrize("d", [128, 3072])
+def test_head_rows_with_an_outlier_first_value(dev, d):
+    """The narrowest and the widest model on rows whose mean is 40 standard deviations from zero, some
+    with a first value (the shift of the folded LayerNorm) 900 from the mean."""
+    import torch
+    from paper_2608_16354_amd import api
+    m = _shape(d, 2, (3, 7, 9))
+    W = I.Weights(m, 152)
+    dm, ws = api.DeviceModel(_Head(W), dev), api.Workspace(m, 1, dev)
+    g, x = I.hidden_state(m, (74,)), I.latent(m, 152, 0)
+    g[: m.n_v] += np.float32(40 * 0.16)
+    g[: m.n_v: 7, 0] += np.float32(900 * 0.16)
+    hm = mod_input(m, (75,))[:2]
+    dx = t(x[None], dev)
+    say("head outlier rows", d)
+    api.dc_head_euler(dm, t(hm, dev), t(g[None], dev), dx, -0.02, [0], ws)
+    torch.cuda.synchronize()
+    v = dit.head(dit.Params(W), hm.astype(np.float64), g[: m.n_v].astype(np.float64))
+    want = dit.euler(x.astype(np.float64), v, 0.52, 0.5)
+    err = rel_l2(dx[0].cpu().numpy() - x, want - x)
+    say("head update rel-L2 (outliers)", err)
+    # a row's first value lies at most sqrt(d) = 55 of its own standard deviations from its mean,
+    # so y keeps 55 x 2^-17 of the result
+    assert err < 55 * 2.0 ** -17
 
 
 @pytest.mark.parametrize("d, lat", [(128, (1, 3, 11)), (768, (2, 9, 9)), (1280, (1, 5, 7)), (2048, (3, 7, 11)),
