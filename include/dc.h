@@ -172,9 +172,8 @@ dc_status dc_drift_l1_noalloc(const dc_model_cfg* cfg, const float* h_in, const 
 /* Output interface H_k and the sampler update (Eq. 1): y = LN(g)(1+scale_f)+shift_f
  * on the video rows of g (f32 [B, N, d]), v = unpatchify(y w_head^T + b_head),
  * x[b] += dsigma * v.  head_mod: f32 [2, d] (shift_f, scale_f); x: f32 [B, C, T, H, W].
- * bf16 models with hidden <= 2048 run one pass over g with the projection operand
- * split into two bf16 halves (about fp32 accuracy); wider bf16 models round y to
- * bf16 before the projection. */
+ * bf16 models run one pass over g with the projection operand split into two bf16
+ * halves (about fp32 accuracy). */
 dc_status dc_head_euler(const dc_model_cfg* cfg, const dc_model_weights* w,
                         const float* head_mod, const float* g, float* x, float dsigma,
                         const int32_t* idx, int32_t n, void* ws, size_t ws_bytes,
@@ -248,8 +247,9 @@ dc_status dc_select_anchors(const double* L, const double* Theta, int32_t n, dou
  * Anchor calibration of the run tables (Sec. 3.1 after Eq. 4; Eq. 5-7).
  * ------------------------------------------------------------------------- */
 
-/* Bytes of device workspace dc_calibrate_tables needs for K steps (the full trace of
- * x_k, u_k, r_k plus the tangent-mode activations of one network pass). */
+/* Bytes of device workspace dc_calibrate_tables needs for K steps: the full trace of
+ * x_k, u_k, r_k plus the activations of one network pass and of the tangents that go
+ * through it together (as many as make about 4,096 rows, from 1 to 32). */
 size_t dc_calibrate_workspace_bytes(const dc_model_cfg* cfg, int32_t K);
 
 /* The response and drift tables of one anchor clip, from its full (uncached) denoising
