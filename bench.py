@@ -75,6 +75,16 @@ def hbm_bytes(m):
     }
 
 
+def scenes_at_once(realized, drift):
+    """Scenes that one sample (realized, drift: [K, B]) takes through the kernels whose launches
+    serve every selected scene at once: patch embedding, drift, cache store and cache apply.
+    (The others have a launch per scene.)"""
+    import numpy as np
+    n_reuse, n = int(np.sum(realized)), int(np.size(realized))
+    return {"patch_embed": n, "drift": int(np.sum(~np.isnan(drift))) + n - n_reuse,
+            "cache_store": n - n_reuse, "cache_apply": n_reuse}
+
+
 def attention_flops(m):
     """Algorithmic FLOPs of one attention launch (one scene, all heads): QK^T and PV."""
     return 4.0 * m.n_tok * m.n_tok * m.hidden
@@ -295,11 +305,7 @@ def main():
                                    "per_kernel_avg_us": {c: 1000.0 * kstats[c][1] / max(kstats[c][0], 1)
                                                          for c in mm}}
         hb = hbm_bytes(m)
-        # scenes processed per class over the timed samples: one launch per scene, except the
-        # drift, cache-store and cache-apply launches, which take every selected scene at once
-        n_checks = int(np.sum(~np.isnan(last["drift"])))
-        n_reuse = int(realized.sum())
-        units = {"drift": n_checks + n_refresh, "cache_store": n_refresh, "cache_apply": n_reuse}
+        units = scenes_at_once(realized, last["drift"])
         out["hbm_kernels"] = {}
         for c, nbytes in hb.items():
             n_c, ms_c = kstats[c]

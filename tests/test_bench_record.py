@@ -48,3 +48,10 @@ def test_algorithmic_counts_at_the_bench_shape():
     assert hb["cache_store"] == 17550 * 1920 * 10
     assert hb["head_reuse"] == 17550 * 1920 * 6 + 2 * 4 * 16 * 13 * 60 * 90
     assert hb["drift"] == 17550 * 1920 * 6
+
+
+def test_scenes_of_launches_that_serve_all_at_once():
+    # two scenes over three steps: 2 reuses, 4 refreshes, 3 drift checks (one vetoed)
+    realized = np.array([[0, 0], [1, 0], [0, 1]], np.uint8)
+    drift = np.array([[np.nan, np.nan], [0.1, 0.9], [np.nan, 0.2]])
+    assert bench.scenes_at_once(realized, drift) == {"patch_embed": 6, "drift": 7, "cache_store": 4, "cache_apply": 2}
