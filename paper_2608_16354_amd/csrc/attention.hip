@@ -1159,7 +1159,8 @@ static Status launch_keys(const uint16_t* qk, const uint16_t* vt, int ldv, uint1
 //    34.5; head_dim 72, 2,000 x 16 (512) 29.2 and 38.2, 3,000 x 16 (752) 64.7 and 57.7;
 //  - k_attn16 (head_dim 64) from 2.25 items of 128 queries per compute unit: 5,000 x 48 (1,920
 //    items) 276, k_attn_bf16 304; 2,500 x 30 (600) 56.9 and 57.7; 5,000 x 12 (480) 87 and 80.5;
-//    17,776 x 30 1,916 and 2,127;
+//    17,776 x 30 1,916 and 2,127.  How the last rounds fill shifts that by up to 3 % either way:
+//    3,597 x 30 (870) 115 and 111.5, 17,000 x 4 (532) 338 and 343;
 //  - k_attn_bf16 between, and for head_dim 72.
 AttnKernel attention_kernel(int head_dim, int heads, int tokens, int cus) {
   if (tokens > 64 && int64_t(heads) * ((tokens + 63) / 64) <= 2 * int64_t(cus)) return AttnKernel::kKeys;

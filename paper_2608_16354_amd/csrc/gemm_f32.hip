@@ -12,7 +12,8 @@
 //  - k_gemm_f32_lds: 64 x 64 tiles through LDS, for everything larger.
 // Against the SIMT kernel this replaced (64 x 64 tile, LDS, no K split), us on MI355X:
 //   272 x 256, K 256: 20.5 -> 3.7;  K 1024: 71 -> 7.5;  2400 x 768, K 3072: 101.7 (111 TFLOP/s);
-//   50 x 11520, K 1920: 220 -> 33.5 (88 MB of weights: 2.6 TB/s).
+//   50 x 11520, K 1920: 220 -> 33.5 called back to back (88 MB of weights: 2.6 TB/s); 40 once a
+//   sample, with the weights in memory only (2.2 TB/s).
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -324,8 +325,8 @@ Status launch(const float* A, int lda, const WT* W, int ldw, int M, int N, int K
 //  - through LDS from about 3/4 of a round of 64 x 64 tiles: 640 x 1536, K 512 (240 tiles) 14.2,
 //    32 x 32 18.6; 1000 x 512, K 2048 (128 tiles) 42.3, 32 x 32 34.3;
 //  - 64 x 48 for 33 to 128 rows and many columns: every weight read once or twice and three
-//    products per load of A (50 x 11520, K 1920: 33.5, 32 x 16 62, LDS 40; 50 x 1920 (40
-//    tiles): 33.4, 32 x 16 12.9);
+//    products per load of A (50 x 11520, K 1920, back to back: 33.5, 32 x 16 62, LDS 40; 50 x 1920
+//    (40 tiles): 33.4, 32 x 16 12.9);
 //  - 32 x 16 while its tiles fit one round (272 x 256, K 1024: 7.5, 32 x 32 10.0), else 32 x 32
 //    (544 x 256, K 1024: 10.1, 32 x 16 12.7).
 // bf16 weights (calibration only) take the direct tiles.
