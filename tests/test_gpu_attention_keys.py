@@ -3,8 +3,9 @@
 Token counts around its 64-key tiles and 64-query items: two tiles with one key in the second
 (one group's only tile), an odd number of tiles (a group idle in the last step), whole tiles
 only, several steps.  Ordinary logits, and query weights scaled by 64, which spread a row's
-logits over hundreds of log2 units: a later tile lies far above a group's first maximum and
-the workgroup takes its safe pass, and the two groups' maxima differ widely when they merge.
+logits over hundreds of log2 units: a later tile lies far above a group's first maximum, which
+is raised or makes the workgroup take its safe pass, and the two groups' maxima differ widely
+when they merge.
 The block is reduced to its attention (W_o = I, gate1 = 1, gate2 = 0)."""
 import math
 
